@@ -41,8 +41,12 @@
  *   cone projection, A phi and every reduction stay in double.
  *
  * Ownership: the caller owns every buffer it passes; the library keeps no
- * pointer to caller memory after a call returns. A dot_plan owns only small
- * constant tables on its device (transform matrices, eigenvalues, weights).
+ * pointer to caller memory after a call returns. A dot_plan owns small
+ * constant tables on its device (transform matrices, eigenvalues, weights)
+ * and, from its first dot_run on a large 1D or 2D grid, a buffer of D+3 double
+ * planes that its iterations use beside the state (about a sixth of the
+ * state; a batch holds one for its members). Where the device has no memory
+ * left for it, runs take the launches of smaller grids: slower, same results.
  * Streams are hipStream_t passed as void*; NULL means the default stream.
  * All step functions are asynchronous on that stream.
  */
@@ -92,7 +96,7 @@ typedef struct {
                              to a multiple of check_every; 0 selects 1.2 */
   double time_limit_s;    /* wall-clock budget in seconds (0: none). dot_run / dot_batch_run:
                              per call; when it runs out the call returns at its next poll of
-                             the control blocks (every 40 iterations) with term DOT_TIMEOUT
+                             the control blocks (every 40 iterations, at even counts) with term DOT_TIMEOUT
                              and the state resumable. Serving: from the request's admission
                              (on its target level); the request is retired at the next step
                              with DOT_TIMEOUT and its iterate so far */

@@ -9,6 +9,7 @@
 #pragma once
 #include "geometry.hpp"
 #include "kernels_dct.hpp"
+#include "kernels_fused.hpp"
 #include "kernels_update.hpp"
 
 namespace dot {
@@ -36,6 +37,16 @@ struct Inst {
   uint32_t blk0;             // first block in the per-node grid
   uint32_t tile0[kMaxAxes];  // first tile in each axis-pass grid
   int32_t tri;               // last axis solved by tridiagonal elimination (else transform, 1/Lambda, transform)
+  // one-sweep iteration: the second place of beta and alpha (the first is beta
+  // and alpha above), the plane of its right-hand side and, at checks, of each
+  // cell's |z - B F q_new - d|^2, and its workgroups
+  BetaPlanes<T> beta2;
+  double* alpha2;
+  T* rhs2;
+  double* ssq;
+  double* ckpt;              // c' checkpoints of the one-lane elimination (W plane 0 without it)
+  FuseGeo fg;
+  uint32_t fblk0;            // first block in the fused grid
 };
 
 // Instance of logical block L: map[L], or 0 without a map (an executor of
@@ -136,26 +147,47 @@ kb_cone_rhs(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int
   rhs_body<T, D, DEFECT>(s.g, s.q[par], s.alpha, s.phi, s.c_lo, s.c_hi, s.work, inv_sigma, L - s.blk0);
 }
 
+// The whole iteration outside the Poisson solve in one sweep (kernels_fused.hpp):
+// alpha and beta from their place `par` (0: alpha, beta; 1: alpha2, beta2) into
+// the other one, q[par] into q[par ^ 1].
+template <typename T, int D, bool DEFECT, bool RHS, bool SSQ>
+__global__ void __launch_bounds__(fuse_max_lanes(), 2)
+kb_fuse(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int par) {
+  const uint32_t L = xcd_remap32(blockIdx.x, gridDim.x);
+  const Inst<T>& s = I[inst_of_block(map, L)];
+  if (stopped(s)) return;
+  const BetaPlanes<T> home{s.beta, s.beta + (size_t)(4 * D) * (size_t)s.g.nb};
+  fuse_body<T, D, DEFECT, RHS, SSQ>(s.g, s.fg, s.phi, s.q[par], s.q[par ^ 1], par ? s.beta2 : home,
+                                    par ? home : s.beta2, par ? s.alpha2 : s.alpha, par ? s.alpha : s.alpha2, s.sw,
+                                    s.om, s.c_lo, s.c_hi, s.rhs2, s.ssq, s.ctl, L - s.fblk0);
+}
+
 // Right-hand side (or its defect against phi) of the Poisson solve into the
-// transform work plane, from (q[par], alpha).
+// transform work plane, from (q[par], alpha); place: where alpha is.
 template <typename T, int D, bool DEFECT>
 __global__ void __launch_bounds__(256)
-kb_rhs(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int par, double sigma_arg) {
+kb_rhs(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int par, double sigma_arg, int place) {
   const uint32_t L = xcd_remap(blockIdx.x, gridDim.x);
   const Inst<T>& s = I[inst_of_block(map, L)];
   if (stopped(s)) return;
   const double inv_sigma = 1.0 / (s.ctl ? glob(s.ctl)->sigma : sigma_arg);
-  rhs_body<T, D, DEFECT>(s.g, s.q[par], s.alpha, s.phi, s.c_lo, s.c_hi, s.work, inv_sigma, L - s.blk0);
+  rhs_body<T, D, DEFECT>(s.g, s.q[par], place ? s.alpha2 : s.alpha, s.phi, s.c_lo, s.c_hi, s.work, inv_sigma,
+                         L - s.blk0);
 }
 
-// Residual partials at the iterate held in q[par] (the newest q).
-template <typename T, int D>
+// Residual partials at the iterate held in q[par] (the newest q). SSQ: slot 11
+// (|z - B F q - d|^2) from the cells' plane that the one-sweep iteration wrote,
+// with alpha and beta at `place`; otherwise kb_beta has filled it.
+template <typename T, int D, bool SSQ>
 __global__ void __launch_bounds__(256)
-kb_resid(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int par) {
+kb_resid(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int par, int place) {
   const uint32_t L = xcd_remap(blockIdx.x, gridDim.x);
   const Inst<T>& s = I[inst_of_block(map, L)];
   if (stopped(s)) return;
-  resid_body<T, D>(s.g, s.phi, s.q[par], s.alpha, s.beta, s.om, s.sw, s.c_lo, s.c_hi, s.partials, L - s.blk0);
+  const BetaPlanes<T> home{s.beta, s.beta + (size_t)(4 * D) * (size_t)s.g.nb};
+  const bool alt = SSQ && place;
+  resid_body<T, D, SSQ>(s.g, s.phi, s.q[par], alt ? s.alpha2 : s.alpha, alt ? s.beta2 : home, s.om, s.sw, s.c_lo,
+                        s.c_hi, s.ssq, s.partials, L - s.blk0);
 }
 
 // First stage of the residual reduction: kFinChunks blocks per instance
@@ -187,20 +219,21 @@ kb_axis_pass(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, in
   PassArgs pa;
   pa.inner = s.g.stride[axis];
   pa.ncols = s.g.nb / s.g.N[axis];
-  axis_pass_body<T, D, KIND, SRC, DST, CW>(s.g, pa, s.tab[axis], s.work, s.phi, s.lam_other, s.lam_last,
-                                           (int64_t)(L - s.tile0[axis]));
+  axis_pass_body<T, D, KIND, SRC, DST, CW>(s.g, pa, s.tab[axis], SRC == kSrcAlt ? s.rhs2 : nullptr, s.work, s.phi,
+                                           s.lam_other, s.lam_last, (int64_t)(L - s.tile0[axis]));
 }
 
 // Last-axis tridiagonal solve over the tiles of the last-axis grid (CW lines
-// each); the c' checkpoints go to W plane 0 (an executor with such an
-// instance runs the cone step after the phi-step, not beside it).
+// each); the c' checkpoints go to W plane 0 where the separate sweeps run (an
+// executor with such an instance runs the cone step after the phi-step, not
+// beside it), to a buffer of their own where W holds the second place of beta.
 template <typename T, int D, int CW>
 __global__ void __launch_bounds__(kTriThreads)
 kb_tri_pass(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map) {
   const uint32_t L = xcd_remap(blockIdx.x, gridDim.x);
   const Inst<T>& s = I[inst_of_block(map, L)];
   if (stopped(s) || !s.tri || s.g.N[D] <= kTriPartMaxNodes) return;  // shorter lines: kb_tri_part
-  tri_pass_body<T, CW>(s.g, s.work, s.W, s.lam_other, (int64_t)(L - s.tile0[D]));
+  tri_pass_body<T, CW>(s.g, s.work, s.ckpt, s.lam_other, (int64_t)(L - s.tile0[D]));
 }
 
 // Partitioned last-axis solve (lines of up to kTriPartMaxNodes nodes) over the

@@ -2,9 +2,10 @@
 // (arXiv 2505.05424, Algorithm 2). See include/dotsocp.h for the contract.
 //
 // Every iteration is a fixed sequence of launches: the right-hand side sweep
-// (or nothing, when the previous iteration's beta launch computed it), 2D+1
+// (or nothing, when the previous iteration's last sweep computed it), 2D+1
 // cosine-transform passes (the last-axis one a tridiagonal solve for long last
-// axes), three update sweeps, and at residual checks two reduction kernels.
+// axes), one sweep for all other steps (large 1D and 2D runs,
+// kernels_fused.hpp) or three, and at residual checks two reduction kernels.
 // Each launch covers all instances of an executor: one plan (dot_run, a batch
 // of one) or a batch (dot_batch_run), through the descriptor arrays of
 // batch.hpp.
@@ -133,6 +134,7 @@ struct GraphCache {
   hipEvent_t fork = nullptr, join = nullptr;  // branch points (no timing)
   bool enabled = true;
   bool warm = false;
+  bool fused = false;  // the captured iterations are one-sweep iterations
   ~GraphCache() {
     if (exec) (void)hipGraphExecDestroy(exec);
     if (exec_poll) (void)hipGraphExecDestroy(exec_poll);
@@ -203,6 +205,10 @@ struct dot_plan {
   double* step_partials = nullptr;
   void* step_scratch = nullptr;  // FP32 transform plane (mixed precision)
   Ctl* host_ctl = nullptr;       // pinned
+  // one-sweep iterations: box and time run of a workgroup, and what they need
+  // beside the state (fuse_layout), allocated at the first run
+  FuseGeo fg{};
+  void* fuse_ws = nullptr;
   // state layout (byte offsets): phi (FP64) | transform scratch (mixed only) |
   // q | q_new | alpha | beta | W (bulk scalar type) | control block | partials
   int n_planes = 0;  // bulk-type planes
@@ -235,6 +241,30 @@ StateLayout state_layout(int D, int64_t nb, int precision) {
   l.off_w = l.off_beta + (size_t)K * pb;
   l.off_dw = align256(l.off_w + (size_t)(4 * D) * pb);
   l.ctl_offset = align256(l.off_dw + (size_t)nb * sizeof(double));
+  return l;
+}
+
+// What the one-sweep iterations of one instance need beside its state (byte
+// offsets in a buffer of the plan or batch): the second places of alpha and of
+// the last two beta components (FP64; the first 4D are the W planes, and the
+// right-hand side is the dw plane, both free in these iterations; in mixed
+// precision the dw plane holds the two components), a plane of the cells'
+// |z - B F q_new - d|^2 (mixed; FP64: the dw plane at checks) and the c'
+// checkpoints of the one-lane elimination.
+struct FuseLayout {
+  size_t alpha = 0, hi = 0, ssq = 0, ckpt = 0, bytes = 0;
+};
+FuseLayout fuse_layout(const dot_plan* P) {
+  const size_t plane = align256((size_t)P->g.nb * sizeof(double));
+  FuseLayout l;
+  l.hi = align256((size_t)(P->D + 1) * P->g.nb * sizeof(double));
+  l.ssq = l.hi + (P->precision == DOT_FP64 ? align256(2 * (size_t)P->g.nb * sizeof(double)) : 0);
+  l.ckpt = l.ssq + (P->precision == DOT_FP64 ? 0 : plane);
+  l.bytes = l.ckpt;
+  if (P->tri && P->g.N[P->D] > kTriPartMaxNodes) {
+    const int64_t L = P->g.N[P->D];
+    l.bytes += align256((size_t)((L + kTriChunk - 1) / kTriChunk) * (size_t)(P->g.nb / L) * sizeof(double));
+  }
   return l;
 }
 
@@ -541,6 +571,133 @@ void set_sweep(Geo& g, int tc) {
 // Workgroups of a flat sweep (one lane per plane entry).
 unsigned flat_grid(const dot_plan* P) { return (unsigned)((P->g.nb + kBlock - 1) / kBlock); }
 
+// Distinct values of ceil(n / k), k = 1, 2, ..., not above `most`: the sizes that
+// cut n nodes into equal parts.
+std::vector<int> even_parts(int n, int most) {
+  std::vector<int> v;
+  for (int k = 1; k <= n; ++k) {
+    const int p = (n + k - 1) / k;
+    if (p <= most && (v.empty() || v.back() != p)) v.push_back(p);
+  }
+  return v;
+}
+
+// Boxes that the workgroups of the one-sweep iteration may take on a grid (the
+// fields of FuseGeo but for the time run).
+std::vector<FuseGeo> fuse_boxes(const Geo& g) {
+  const int D = g.D, cap = fuse_max_lanes();
+  const int wide = D > 1 ? 62 : cap - 2;
+  std::vector<int> rows = even_parts(g.N[D], wide);
+  for (int r : {14, 30, 62, 126, 254, 510})
+    if (r < g.N[D] && r <= wide) rows.push_back(r);
+  const std::vector<int> cols = D > 1 ? even_parts(g.N[1], 64) : std::vector<int>{1};
+  std::vector<FuseGeo> out;
+  for (int r : rows)
+    for (int c : cols) {
+      FuseGeo f{};
+      f.ni = r * c;
+      f.lanes = D > 1 ? c * (r + 2) + 2 * r : r + 2;
+      if (f.lanes > cap) continue;
+      for (int d = 0; d < kMaxAxes; ++d) f.a[d] = f.nt[d] = 1;
+      f.a[D] = r;
+      if (D > 1) f.a[1] = c;
+      f.ntile = 1;
+      for (int d = 1; d <= D; ++d) {
+        f.nt[d] = (g.N[d] + f.a[d] - 1) / f.a[d];
+        f.ntile *= (uint32_t)f.nt[d];
+      }
+      out.push_back(f);
+    }
+  return out;
+}
+int fuse_waves(const FuseGeo& f) { return (f.lanes + 63) / 64; }
+void fuse_run(FuseGeo& f, const Geo& g, int tc) {
+  f.tc = tc;
+  f.nblk = f.ntile * (uint32_t)((g.N[0] + tc - 1) / tc);
+}
+// Cost of a round of workgroups per time slice, from measured launches: it
+// grows with the waves beside each other on a CU, since the launch is bound by
+// the bytes they move.
+double fuse_round(double waves_per_cu) { return 0.4 * waves_per_cu + 0.35; }
+// A workgroup's time slices: two more than it owns, and its start.
+double fuse_slices(int tc) { return tc + 4.0; }
+// A short row of the box (contiguous nodes) costs more per node, for the
+// partly used cache lines at its ends.
+double fuse_row(const Geo& g, const FuseGeo& f) { return 1.0 + 4.0 / f.a[g.D]; }
+
+// Box and time run of the one-sweep iteration of one instance: the pair with
+// the fastest launch in that model, round by round (kFuseWaves waves are
+// resident per CU). 2D 64x256^2, mixed / FP64, us per iteration: boxes of 10x30
+// nodes over all 65 time nodes (234 workgroups, one round) 374 / 512, over 33
+// (two rounds) 389 / 558, 6x30x13 401 / 591, 9x30x65 (261 workgroups: a second
+// round for 5 of them) 515 / 667.
+constexpr int kFuseCUs = 256, kFuseWaves = 8;
+FuseGeo fuse_shape(const Geo& g) {
+  const std::vector<int> runs = even_parts(g.N[0], g.N[0]);
+  FuseGeo best{};
+  double least = 0.0;
+  for (FuseGeo f : fuse_boxes(g)) {
+    const int waves = fuse_waves(f);
+    const double room = (double)kFuseCUs * std::max(1, kFuseWaves / waves);
+    auto round_cost = [&](double blocks) { return fuse_round(waves * std::ceil(blocks / kFuseCUs)); };
+    for (int tc : runs) {
+      fuse_run(f, g, tc);
+      const double full = std::floor(f.nblk / room), rest = f.nblk - full * room;
+      const double t = (full * round_cost(room) + (rest > 0.0 ? round_cost(rest) : 0.0)) * fuse_slices(tc) *
+                       fuse_row(g, f);
+      if (best.nblk && t >= least) continue;
+      least = t;
+      best = f;
+    }
+  }
+  return best;
+}
+
+// The same for the instances of a batch, whose workgroups share one size: 4
+// waves (two workgroups per CU), 8 in large batches (less halo); other sizes
+// leave waves of a CU unused (heterogeneous 2D batches of 4 / 12 / 32 members,
+// mixed, us per iteration: 4 waves 100 / 282 / 640, 8 waves 104 / 285 / 620, 5
+// waves 113 / 305 / 668). The bound on the time runs with the least sum of the
+// average and the longest work per resident workgroup.
+constexpr int64_t kFuseWideNodes = int64_t(1) << 22;
+std::vector<FuseGeo> fuse_shapes(dot_plan* const* plans, int count) {
+  if (count == 1) return {fuse_shape(plans[0]->g)};
+  int64_t nodes = 0;
+  int longest = 1;
+  for (int i = 0; i < count; ++i) {
+    nodes += plans[i]->g.nb;
+    longest = std::max(longest, plans[i]->g.N[0]);
+  }
+  const int waves = nodes >= kFuseWideNodes ? 8 : 4;
+  std::vector<FuseGeo> best, cur((size_t)count);
+  for (int i = 0; i < count; ++i) {
+    double least = 0.0;
+    for (const FuseGeo& f : fuse_boxes(plans[i]->g)) {
+      const double c = f.ntile * fuse_row(plans[i]->g, f);
+      if (f.lanes > 64 * waves || (cur[i].ni && c >= least)) continue;
+      least = c;
+      cur[i] = f;
+    }
+  }
+  double least = 0.0;
+  for (int most = 2; most < 2 * longest; most *= 2) {
+    double sum = 0.0, last = 0.0;
+    for (int i = 0; i < count; ++i) {
+      const Geo& g = plans[i]->g;
+      const int parts = (g.N[0] + most - 1) / most;
+      fuse_run(cur[i], g, (g.N[0] + parts - 1) / parts);
+      const double one = fuse_slices(cur[i].tc) * fuse_row(g, cur[i]);
+      sum += one * cur[i].nblk;
+      last = std::max(last, one);
+    }
+    const double t = sum / (double)(kFuseCUs * (kFuseWaves / waves)) + last;
+    if (!best.empty() && t >= least) continue;
+    least = t;
+    best = cur;
+  }
+  return best;
+}
+
 FinArgs fin_args(const dot_plan* P) {
   FinArgs fa;
   fa.vol = P->vol;
@@ -576,8 +733,24 @@ Inst<T> inst_of(const dot_plan* P, double* phi, T* scr, T* q, T* qn, double* alp
   s.lam_last = (const T*)P->lam_last;
   for (int a = 0; a < kMaxAxes; ++a) s.tab[a] = tab_of<T>(P, a);
   s.fa = fin_args(P);
+  s.ckpt = reinterpret_cast<double*>(W);
   s.tri = P->tri;
   return s;
+}
+
+// What the one-sweep iterations add to the descriptor of an instance with its
+// state at `state`: `ws` holds fuse_layout(P).
+template <typename T>
+void fuse_fields(Inst<T>& s, const dot_plan* P, const FuseGeo& f, void* ws) {
+  const FuseLayout l = fuse_layout(P);
+  constexpr bool kMixed = !std::is_same<T, double>::value;
+  s.alpha2 = at<double>(ws, l.alpha);
+  s.beta2.lo = s.W;
+  s.beta2.hi = kMixed ? reinterpret_cast<T*>(s.dw) : at<T>(ws, l.hi);
+  s.rhs2 = kMixed ? s.work : reinterpret_cast<T*>(s.dw);
+  s.ssq = kMixed ? at<double>(ws, l.ssq) : s.dw;
+  s.ckpt = at<double>(ws, l.ckpt);
+  s.fg = f;
 }
 
 // Descriptor of an instance whose state buffer (plan layout) is at `state`
@@ -620,6 +793,10 @@ struct Exec {
   int ntri = 0;       // instances whose last axis takes the tridiagonal solve
   int ntri_long = 0;  // of those, lines longer than the partitioned solve takes
   int64_t nodes = 0;  // grid nodes over all instances
+  bool fused = false;  // one-sweep iterations (descriptors carry fuse_fields)
+  const uint16_t* map_fuse = nullptr;
+  unsigned grid_fuse = 0;
+  int lanes_fuse = 0;  // workgroup size
   Prof* prof = nullptr;
   int device = 0;
   struct GraphCache* graphs = nullptr;  // captured 10-iteration blocks (nullptr: plain launches)
@@ -712,11 +889,11 @@ int run_passes(const Exec& E, int par, double sigma, hipStream_t st) {
 // phi. Mixed: the FP32 transforms solve A^*A dphi = b - A^*A phi on the
 // scratch plane and the last pass adds dphi to the FP64 phi.
 template <typename T, int D, bool DEFECT>
-int launch_rhs(const Exec& E, int par, double sigma, hipStream_t st) {
+int launch_rhs(const Exec& E, int par, double sigma, hipStream_t st, int place = 0) {
   {
     ProfScope ps(E.prof, DOT_K_RHS, st);
     hipLaunchKernelGGL((kb_rhs<T, D, DEFECT>), dim3(E.grid_nodes), dim3(kBlock), 0, st, (const Inst<T>*)E.d_inst,
-                       E.map_nodes, par, sigma);
+                       E.map_nodes, par, sigma, place);
   }
   HIP_OK(hipGetLastError());
   return DOT_OK;
@@ -797,12 +974,12 @@ int update_iter(const Exec& E, int par, int check, hipStream_t st, bool rhs_next
 // Residual partials at the iterate in q[qpar], the first stage of their
 // reduction (kFinChunks blocks per instance; large instances only), then one
 // finalize block per instance.
-template <typename T, int D>
-int check_iter(const Exec& E, int qpar, int update_ctl, hipStream_t st) {
+template <typename T, int D, bool SSQ = false>
+int check_iter(const Exec& E, int qpar, int update_ctl, hipStream_t st, int place = 0) {
   const Inst<T>* I = (const Inst<T>*)E.d_inst;
   {
     ProfScope ps(E.prof, DOT_K_RESID, st);
-    hipLaunchKernelGGL((kb_resid<T, D>), dim3(E.grid_nodes), dim3(kBlock), 0, st, I, E.map_nodes, qpar);
+    hipLaunchKernelGGL((kb_resid<T, D, SSQ>), dim3(E.grid_nodes), dim3(kBlock), 0, st, I, E.map_nodes, qpar, place);
   }
   HIP_OK(hipGetLastError());
   {
@@ -820,12 +997,81 @@ int check_iter(const Exec& E, int qpar, int update_ctl, hipStream_t st) {
 // What one iteration hands to the next inside a launch sequence: its
 // right-hand side and its z-step already computed by the previous beta
 // launch (sequential order), or the previous beta update still to run, fused
-// with this iteration's z-step (overlapped order).
+// with this iteration's z-step (overlapped order); place: where alpha and
+// beta are (1: their second place, between one-sweep iterations).
 struct Carry {
   bool rhs_ready = false;
   bool cone_ready = false;
   bool beta_pending = false;
+  int place = 0;
 };
+
+// The one-sweep iteration (kernels_fused.hpp) of parity par; `rhs`: with the
+// next right-hand side, `check`: with the cells' sums for the residual sweep.
+template <typename T, int D>
+int launch_fuse(const Exec& E, int par, bool rhs, bool check, hipStream_t st) {
+  if constexpr (D < 3) {
+    constexpr bool kMixed = !std::is_same<T, double>::value;
+    const Inst<T>* I = (const Inst<T>*)E.d_inst;
+    const dim3 grid(E.grid_fuse), block(E.lanes_fuse);
+    if (check)
+      hipLaunchKernelGGL((kb_fuse<T, D, kMixed, false, true>), grid, block, 0, st, I, E.map_fuse, par);
+    else if (rhs)
+      hipLaunchKernelGGL((kb_fuse<T, D, kMixed, true, false>), grid, block, 0, st, I, E.map_fuse, par);
+    else
+      hipLaunchKernelGGL((kb_fuse<T, D, kMixed, false, false>), grid, block, 0, st, I, E.map_fuse, par);
+    HIP_OK(hipGetLastError());
+    return DOT_OK;
+  }
+  return fail(DOT_EINVAL, "no one-sweep iteration in three dimensions");
+}
+
+// Whether a run over `nodes` grid nodes in all takes one-sweep iterations: from
+// the sizes where the bytes they save outweigh their longer chain per time
+// slice. us per iteration, separate sweeps -> one sweep; FP64: 2D 32x64^2 (0.14 M
+// nodes) 51.3 -> 53.3, 60x70x65 (0.29 M) 69.5 -> 67.7, 32x96^2 (0.31 M) 71.0 ->
+// 65.8, 64x256^2 (4.3 M) 697 -> 515, 32x1024^2 7395 -> 5313; mixed: 24x45x83
+// (0.10 M) 40.2 -> 46.2, 64x64x100 (0.43 M) 71.0 -> 74.2, 32x128^2 (0.55 M) 98.8 ->
+// 92.5, 64x256^2 449 -> 365, 32x1024^2 4582 -> 3443. Batches of small grids have
+// more halo: heterogeneous 2D batches, FP64: 5 members (1.0 M) 205 -> 208, 8
+// (1.8 M) 368 -> 341, 64 (11.5 M) 1823 -> 1418; mixed: 8 228 -> 245, 12 (2.4 M) 294 ->
+// 283, 64 1088 -> 972. In three dimensions the halo of a box that fits a
+// workgroup about doubles its cells (3D 32x64^3 mixed 1162 -> 1409): separate
+// sweeps.
+bool fuse_pays(int D, int precision, int count, int64_t nodes) {
+  const int64_t least = precision == DOT_FP64 ? (count == 1 ? int64_t(1) << 18 : int64_t(5) << 18)
+                                              : (count == 1 ? int64_t(1) << 19 : int64_t(1) << 21);
+  return D < 3 && nodes >= least;
+}
+
+// Whether an executor runs one-sweep iterations (kernel classes timed one by
+// one run as separate sweeps).
+bool one_sweep(const Exec& E) { return E.fused && !(E.prof && E.prof->cls >= 0); }
+
+// Iteration `it` as a right-hand side (unless the previous sweep left it), the
+// transform passes and one sweep. alpha and beta are at place it & 1 before it
+// and at the other one after it.
+template <typename T, int D>
+int fused_iter(const Exec& E, int it, hipStream_t st, bool more, Carry* cy) {
+  constexpr bool kMixed = !std::is_same<T, double>::value;
+  const int par = it & 1;
+  const int check = ((it + 1) % E.cadence) == 0;
+  int rc;
+  if (!cy->rhs_ready && (rc = launch_rhs<T, D, kMixed>(E, par, 0.0, st, par))) return rc;
+  if constexpr (kMixed)
+    rc = run_passes<T, D, kSrcPlane, kDstPhiAdd>(E, par, 0.0, st);
+  else
+    rc = cy->rhs_ready ? run_passes<double, D, kSrcAlt, kDstPlane>(E, par, 0.0, st)
+                       : run_passes<double, D, kSrcPlane, kDstPlane>(E, par, 0.0, st);
+  if (rc) return rc;
+  const bool rhs = !check && more;
+  if ((rc = launch_fuse<T, D>(E, par, rhs, check, st))) return rc;
+  if (check && (rc = check_iter<T, D, true>(E, par ^ 1, 1, st, par ^ 1))) return rc;
+  cy->rhs_ready = rhs;
+  cy->cone_ready = cy->beta_pending = false;
+  cy->place = par ^ 1;
+  return DOT_OK;
+}
 
 // Whether the executor runs the z-step beside the phi-step: needs the branch
 // streams, no kernel class being timed, no instance whose last axis takes the
@@ -839,7 +1085,7 @@ struct Carry {
 // 1185 -> 1162 us; the 64-instance 2D batch 1154 -> 1086 us.
 constexpr int64_t kOverlapMinNodes = int64_t(1) << 21;
 bool overlapped(const Exec& E) {
-  return E.graphs && !(E.prof && E.prof->cls >= 0) && E.ntri_long == 0 && E.nodes >= kOverlapMinNodes;
+  return E.graphs && !E.fused && !(E.prof && E.prof->cls >= 0) && E.ntri_long == 0 && E.nodes >= kOverlapMinNodes;
 }
 
 int branch_streams(GraphCache* g) {
@@ -871,8 +1117,16 @@ int branch_streams(GraphCache* g) {
 // An iteration with a check, or the last one of a sequence (`more` false),
 // runs its beta update alone, so that every sequence ends with a complete
 // iterate. All orders compute the same values.
+//
+// One-sweep executors: every iteration whose alpha and beta are at place
+// it & 1 runs as fused_iter. A call that starts at an odd count finds them at
+// place 0; that one iteration runs as separate sweeps, complete in itself.
 template <typename T, int D>
 int one_iter(const Exec& E, int it, hipStream_t st, hipStream_t side, bool more, Carry* cy) {
+  if (one_sweep(E)) {
+    if (cy->place == (it & 1)) return fused_iter<T, D>(E, it, st, more, cy);
+    more = false;
+  }
   const int par = it & 1;
   const int check = ((it + 1) % E.cadence) == 0;
   int rc;
@@ -981,6 +1235,10 @@ int run_iters(const Exec& E, int it0, int max_iters, const void* ctl_dev, size_t
       if (!reinterpret_cast<const Ctl*>(static_cast<const char*>(ctl_host) + i * ctl_stride)->stop) return false;
     return true;
   };
+  if (E.graphs && E.graphs->fused != one_sweep(E)) {
+    drop_graph(*E.graphs);
+    E.graphs->fused = one_sweep(E);
+  }
   bool use_graphs = E.graphs && E.graphs->enabled && !(E.prof && E.prof->cls >= 0) && E.cadence == 5;
   int capture_failures = 0;
   hipStream_t side = nullptr;
@@ -990,13 +1248,15 @@ int run_iters(const Exec& E, int it0, int max_iters, const void* ctl_dev, size_t
     side = E.graphs->side;
   }
   int j = 0;
-  int since_poll = 0;
+  // a call that starts at an odd count polls one iteration early, so that at
+  // every poll alpha and beta are at their first place
+  int since_poll = it0 & 1;
   Carry cy;  // what the previous iteration left to this one
   while (j < max_iters) {
     const int it = it0 + j;
     int rc;
     const bool blk_ok = use_graphs && E.graphs->warm && it % kGraphIters == 0 && !cy.rhs_ready &&
-                        !cy.cone_ready && !cy.beta_pending;
+                        !cy.cone_ready && !cy.beta_pending && cy.place == 0;
     // a block replays its captured graph; a capture that fails (nothing of
     // it ran) leaves the block to plain launches, and after two failures this
     // call launches plainly
@@ -1048,6 +1308,7 @@ int run_iters(const Exec& E, int it0, int max_iters, const void* ctl_dev, size_t
       // the executor's layout may change here (nothing is deferred at a poll)
       if (on_poll && j < max_iters) {
         if ((rc = (*on_poll)())) return rc;
+        if (E.graphs) E.graphs->fused = one_sweep(E);
         side = nullptr;
         if (overlapped(E)) {
           if ((rc = branch_streams(E.graphs))) return rc;
@@ -1125,10 +1386,42 @@ Exec plan_exec(dot_plan* P, int slot) {
     E.smem_axis[a] = ag.smem;
     E.waves_axis[a] = ag.waves;
   }
+  E.fused = slot == 0 && P->fuse_ws && P->fg.nblk;
+  E.grid_fuse = P->fg.nblk;
+  E.lanes_fuse = fuse_waves(P->fg) * 64;
   E.prof = &P->prof;
   E.device = P->device;
   E.graphs = slot == 0 ? &P->graphs : nullptr;
   return E;
+}
+
+// The buffer of the one-sweep iterations, allocated and cleared at the first
+// run (entries outside a plane's set are copied home with it and must be
+// zero). Without the memory for it the separate sweeps run instead, with the
+// same results; the next run asks again.
+void fuse_alloc(void** ws, size_t bytes) {
+  if (*ws) return;
+  DevLock lk(g_dev_mu);
+  if (hipMalloc(ws, bytes) != hipSuccess) {
+    *ws = nullptr;
+  } else if (hipMemset(*ws, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipFree(*ws);
+    *ws = nullptr;
+  }
+  if (!*ws) (void)hipGetLastError();
+}
+
+// alpha and beta of an instance that did an odd number of one-sweep iterations
+// go back to their first place.
+template <typename T>
+int fuse_home(const dot_plan* P, const Inst<T>& s, hipStream_t st) {
+  const Geo& g = P->g;
+  const size_t pb = (size_t)g.nb * sizeof(T), cells = (size_t)g.n[0] * (size_t)g.nx * sizeof(T);
+  HIP_OK(hipMemcpyAsync(s.alpha, s.alpha2, (size_t)(P->D + 1) * g.nb * sizeof(double), hipMemcpyDeviceToDevice, st));
+  HIP_OK(hipMemcpy2DAsync(s.beta, pb, s.beta2.lo, pb, cells, 4 * P->D, hipMemcpyDeviceToDevice, st));
+  HIP_OK(hipMemcpy2DAsync(s.beta + (size_t)(4 * P->D) * g.nb, pb, s.beta2.hi, pb, cells, 2, hipMemcpyDeviceToDevice,
+                          st));
+  return DOT_OK;
 }
 
 template <typename T>
@@ -1144,14 +1437,25 @@ struct RunF {
     HIP_OK(hipMemcpyAsync(P->host_ctl, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     HIP_OK(hipStreamSynchronize(st));
     const int it0 = P->host_ctl->iter;
+    if (fuse_pays(D, P->precision, 1, P->g.nb)) {
+      if (!P->fg.nblk) P->fg = fuse_shape(P->g);
+      fuse_alloc(&P->fuse_ws, fuse_layout(P).bytes);
+    }
     Exec E = plan_exec(P, 0);
-    int rc = upload_inst(E, state_inst<T>(P, state, ctl), st);
+    Inst<T> inst = state_inst<T>(P, state, ctl);
+    if (E.fused) fuse_fields(inst, P, P->fg, P->fuse_ws);
+    int rc = upload_inst(E, inst, st);
     if (rc) return rc;
     if (!P->host_ctl->stop) {
       bool timed_out = false;
       rc = run_iters<T, D>(E, it0, max_iters, ctl, sizeof(Ctl), P->host_ctl, st, nullptr, -1, P->time_limit,
                            &timed_out);
       if (rc) return rc;
+      const int end = P->host_ctl->iter;
+      if (one_sweep(E) && end > it0 && (end & 1)) {
+        if ((rc = fuse_home(P, inst, st))) return rc;
+        HIP_OK(hipStreamSynchronize(st));
+      }
       fill_result(*P->host_ctl, res);
       if (timed_out && !P->host_ctl->stop && res) res->term = DOT_TIMEOUT;
       return DOT_OK;
@@ -1393,6 +1697,8 @@ struct dot_batch {
   Ctl* host_ctl = nullptr;     // pinned, one entry per instance at ctl_stride
   int it = 0;                  // iterations done (all instances in lockstep)
   std::vector<char> active;    // instances laid out in the launch grids (empty: all)
+  std::vector<FuseGeo> fg;     // one-sweep iterations of each instance
+  void* fuse_ws = nullptr;     // their buffer (fuse_layout of each instance, one after another)
   Prof prof;
   GraphCache graphs;
 };
@@ -1434,6 +1740,20 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
     for (int k = 0; k < n; ++k)
       maps.insert(maps.end(), (size_t)tiles_for(plans[k]->lines[a], ag[a].cw), (uint16_t)idx[k]);
   }
+  const size_t fuse_off = maps.size();
+  int64_t all_nodes = 0;
+  for (dot_plan* P : plans) all_nodes += P->g.nb;
+  std::vector<FuseGeo> fg(count);
+  int lanes = 0;
+  if (fuse_pays(B->D, B->precision, n, all_nodes)) {
+    const std::vector<FuseGeo> shapes = fuse_shapes(plans.data(), n);
+    for (int k = 0; k < n; ++k) {
+      fg[idx[k]] = shapes[k];
+      lanes = std::max(lanes, fuse_waves(shapes[k]) * 64);
+      maps.insert(maps.end(), (size_t)shapes[k].nblk, (uint16_t)idx[k]);
+    }
+  }
+  const size_t fuse_blocks = maps.size() - fuse_off;
   uint16_t* fresh = nullptr;
   HIP_OK(hipMalloc((void**)&fresh, maps.size() * sizeof(uint16_t)));
   const hipError_t e = hipMemcpy(fresh, maps.data(), maps.size() * sizeof(uint16_t), hipMemcpyHostToDevice);
@@ -1461,6 +1781,10 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
     E.nstaged += P->nblocks >= kFinStageMinRows ? 1 : 0;
     E.nodes += P->g.nb;
   }
+  B->fg = std::move(fg);
+  E.map_fuse = B->d_maps + fuse_off;
+  E.grid_fuse = (unsigned)fuse_blocks;
+  E.lanes_fuse = lanes;
   E.map_nodes = B->d_maps;
   for (int a = 0; a <= B->D; ++a) {
     E.map_axis[a] = B->d_maps + map_off[a];
@@ -1472,19 +1796,43 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
   return DOT_OK;
 }
 
+// Bytes of the one-sweep buffer of a batch.
+size_t batch_fuse_bytes(const dot_batch* B) {
+  size_t off = 0;
+  for (const dot_plan* P : B->plans) off += align256(fuse_layout(P).bytes);
+  return off;
+}
+
+// Descriptor of instance i (without its blocks in the launch grids); fuse_off:
+// running offset in the one-sweep buffer.
+template <typename T>
+Inst<T> batch_inst(const dot_batch* B, void* ws, int i, size_t* fuse_off) {
+  const dot_plan* P = B->plans[i];
+  Ctl* ctl = reinterpret_cast<Ctl*>(static_cast<char*>(ws) + (size_t)i * B->ctl_stride);
+  Inst<T> s = state_inst<T>(P, static_cast<char*>(ws) + B->state_off[i], ctl);
+  if (B->fuse_ws) {
+    fuse_fields(s, P, B->fg[i], static_cast<char*>(B->fuse_ws) + *fuse_off);
+    *fuse_off += align256(fuse_layout(P).bytes);
+  }
+  return s;
+}
+
 template <typename T>
 int batch_descriptors(dot_batch* B, void* ws, hipStream_t st) {
   const int count = (int)B->plans.size();
   std::vector<Inst<T>> host(count);
-  uint32_t blk = 0;
+  B->E.fused = B->fuse_ws && B->E.grid_fuse;
+  size_t fuse_off = 0;
+  uint32_t blk = 0, fblk = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
   for (int i = 0; i < count; ++i) {
     dot_plan* P = B->plans[i];
-    Ctl* ctl = reinterpret_cast<Ctl*>(static_cast<char*>(ws) + (size_t)i * B->ctl_stride);
-    host[i] = state_inst<T>(P, static_cast<char*>(ws) + B->state_off[i], ctl);
+    host[i] = batch_inst<T>(B, ws, i, &fuse_off);
     if (!laid_out(B, i)) continue;  // no workgroup maps to it (blk0 and tile0 stay 0)
     host[i].blk0 = blk;
     blk += (uint32_t)P->nblocks;
+    host[i].fblk0 = fblk;
+    fblk += B->fg[i].nblk;
     for (int a = 0; a <= B->D; ++a) {
       host[i].tile0[a] = tile[a];
       tile[a] += (uint32_t)tiles_for(P->lines[a], B->E.cw_axis[a]);
@@ -1541,15 +1889,42 @@ struct BatchRunF {
       if (done) *done = 0;
       return DOT_OK;
     }
+    std::vector<int> began(count);  // iteration counts at the start of the call
+    for (int i = 0; i < count; ++i) began[i] = reinterpret_cast<const Ctl*>(hc + (size_t)i * B->ctl_stride)->iter;
+    if (B->E.grid_fuse) fuse_alloc(&B->fuse_ws, batch_fuse_bytes(B));
     int rc = batch_compact<T>(B, ws, st, true);
     if (rc || (rc = batch_descriptors<T>(B, ws, st))) return rc;
     // the smallest time budget of the instances bounds the call
     double limit = 0.0;
     for (auto* P : B->plans)
       if (P->time_limit > 0.0) limit = limit > 0.0 ? std::min(limit, P->time_limit) : P->time_limit;
-    const std::function<int()> compact = [&]() { return batch_compact<T>(B, ws, st, false); };
-    return run_iters<T, D>(B->E, B->it, max_iters, ws, B->ctl_stride, B->host_ctl, st, done, -1, limit, timed_out,
-                           &compact);
+    // alpha and beta of an instance that stopped after an odd number of
+    // one-sweep iterations go back to their first place: at the poll that sees
+    // it (the next layout may run other sweeps), at the end for all
+    std::vector<char> home(count, 0);
+    auto bring_home = [&](bool all) -> int {
+      size_t fuse_off = 0;
+      for (int i = 0; i < count; ++i) {
+        const Inst<T> s = batch_inst<T>(B, ws, i, &fuse_off);
+        const Ctl* c = reinterpret_cast<const Ctl*>(hc + (size_t)i * B->ctl_stride);
+        if (home[i] || !(all || c->stop)) continue;
+        home[i] = 1;
+        const int did = c->iter - began[i];  // in this call, up to where it stopped
+        if (!one_sweep(B->E) || did <= 0 || ((B->it + did) & 1) == 0) continue;
+        const int r = fuse_home(B->plans[i], s, st);
+        if (r) return r;
+      }
+      return DOT_OK;
+    };
+    const std::function<int()> compact = [&]() {
+      const int r = bring_home(false);
+      return r ? r : batch_compact<T>(B, ws, st, false);
+    };
+    rc = run_iters<T, D>(B->E, B->it, max_iters, ws, B->ctl_stride, B->host_ctl, st, done, -1, limit, timed_out,
+                         &compact);
+    if (rc || (rc = bring_home(true))) return rc;
+    HIP_OK(hipStreamSynchronize(st));
+    return DOT_OK;
   }
 };
 
@@ -1780,6 +2155,7 @@ void dot_plan_destroy(dot_plan* P) {
   (void)hipFree(P->step_partials);
   (void)hipFree(P->step_cbuf);
   (void)hipFree(P->step_scratch);
+  (void)hipFree(P->fuse_ws);
   (void)hipHostFree(P->host_ctl);
   delete P;
 }
@@ -2072,6 +2448,7 @@ void dot_batch_destroy(dot_batch* B) {
   for (auto* p : B->plans) dot_plan_destroy(p);
   (void)hipFree(B->d_inst);
   (void)hipFree(B->d_maps);
+  (void)hipFree(B->fuse_ws);
   (void)hipHostFree(B->host_ctl);
   delete B;
 }

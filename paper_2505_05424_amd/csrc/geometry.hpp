@@ -49,6 +49,15 @@ __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t G) {
   return x * q + (x < r ? x : r) + p;
 }
 
+// The same in pieces of 32 logical workgroups, dealt to the XCDs in turn: for
+// launches whose workgroups differ in length from one part of the grid to the
+// next (a contiguous eighth per XCD would give one XCD the long ones).
+__device__ __forceinline__ uint32_t xcd_remap32(uint32_t b, uint32_t G) {
+  const uint32_t even = G & ~255u;
+  if (b >= even) return even + xcd_remap(b - even, G - even);
+  return (b & ~255u) + (b & 7) * 32u + ((b & 255u) >> 3);
+}
+
 // Device-resident control block: penalty, counters, stop flag and the last
 // residuals. Kernels read sigma and stop at entry; the finalize kernel writes.
 constexpr int kSigmaHist = 32;  // sigma changes kept in the control block

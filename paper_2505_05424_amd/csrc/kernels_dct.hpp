@@ -79,8 +79,9 @@ constexpr int items_per_wave() {
 
 enum PassKind { kFwd = 0, kInv = 1, kFwdScaleInv = 2 };
 // What the first (time-axis forward) pass loads: the work plane itself (in
-// place), or an FP64 right-hand side plane (mixed-precision step call).
-enum PassSrc { kSrcPlane = 0, kSrcPlaneF64 = 3 };
+// place), the right-hand side plane of the one-sweep iteration, or an FP64
+// right-hand side plane (mixed-precision step call).
+enum PassSrc { kSrcPlane = 0, kSrcAlt = 1, kSrcPlaneF64 = 3 };
 // Where the last (time-axis inverse) pass stores: the work plane, phi += result
 // (FP64), or phi = result (FP64).
 enum PassDst { kDstPlane = 0, kDstPhiAdd = 1, kDstPhiSet = 2 };
@@ -261,14 +262,15 @@ struct PassArgs {
   int64_t ncols;   // number of lines = outer * inner
 };
 
-// One axis pass over a plane, in place, on tiles of CW lines. SRC and DST
+// One axis pass over a plane, in place (src == plane; kSrcAlt: from src into
+// plane), on tiles of CW lines. SRC and DST
 // other than kSrcPlane / kDstPlane occur on the time axis only (first forward
 // / last inverse pass). KIND = kFwdScaleInv (last axis only) applies forward,
 // 1/Lambda, inverse.
 template <typename T, int D, int KIND, int SRC, int DST, int CW>
 __device__ __forceinline__ void axis_pass_body(const Geo& g, const PassArgs& pa, const AxisTab<T>& a,
-                                               T* __restrict__ plane, double* __restrict__ phi,
-                                               const T* __restrict__ lam_other, const T* __restrict__ lam_last,
+                                               const T* __restrict__ src, T* __restrict__ plane,
+                                               double* __restrict__ phi, const T* __restrict__ lam_other, const T* __restrict__ lam_last,
                                                int64_t blk) {
   extern __shared__ unsigned char smem_raw[];
   T* tile = reinterpret_cast<T*>(smem_raw);
@@ -309,6 +311,9 @@ __device__ __forceinline__ void axis_pass_body(const Geo& g, const PassArgs& pa,
   }
   const uint32_t lbase = (uint32_t)c0 * (uint32_t)L;
   const uint32_t llim = (uint32_t)ncols * (uint32_t)L;
+  auto read = [&](uint32_t o) -> T {
+    return SRC == kSrcPlaneF64 ? (T)ph[o] : (SRC == kSrcAlt ? glob(src)[o] : pl[o]);
+  };
   // load: each thread issues kLoadBatch independent loads before writing
   // them to the tile, so the memory latency is paid once per batch
   if (inner == 1) {
@@ -317,7 +322,7 @@ __device__ __forceinline__ void axis_pass_body(const Geo& g, const PassArgs& pa,
 #pragma unroll
       for (int r = 0; r < kLoadBatch; ++r) {
         const int e = e0 + r * nthr;
-        v[r] = (e < tot && lbase + e < llim) ? (SRC == kSrcPlaneF64 ? (T)ph[lbase + e] : pl[lbase + e]) : T(0);
+        v[r] = (e < tot && lbase + e < llim) ? read(lbase + e) : T(0);
       }
 #pragma unroll
       for (int r = 0; r < kLoadBatch; ++r) {
@@ -335,7 +340,7 @@ __device__ __forceinline__ void axis_pass_body(const Geo& g, const PassArgs& pa,
       for (int r = 0; r < kLoadBatch; ++r) {
         const int j = j0 + r * rstep;
         const uint32_t o = cbase + (uint32_t)j * inner;
-        v[r] = (cok && j < L) ? (SRC == kSrcPlaneF64 ? (T)ph[o] : pl[o]) : T(0);
+        v[r] = (cok && j < L) ? read(o) : T(0);
       }
 #pragma unroll
       for (int r = 0; r < kLoadBatch; ++r) {
@@ -493,7 +498,7 @@ __device__ __forceinline__ double tri_cstep(double lam, double s2, int i, int L,
 // recurrence of each chunk from that checkpoint, so c' never goes through HBM
 // (per point 4 plane accesses instead of 6).
 template <typename T, int CW>
-__device__ __forceinline__ void tri_pass_body(const Geo& g, T* __restrict__ plane, T* __restrict__ cpl,
+__device__ __forceinline__ void tri_pass_body(const Geo& g, T* __restrict__ plane, double* __restrict__ cpl,
                                               const T* __restrict__ lam_other, int64_t blk) {
   const int D = g.D;
   const int L = g.N[D];
@@ -509,7 +514,7 @@ __device__ __forceinline__ void tri_pass_body(const Geo& g, T* __restrict__ plan
   gp<T> pl = glob(plane);
   // checkpoints: nch * ncols doubles, within the plane's nb * sizeof(T) bytes
   // for every L >= 2 (nch = ceil(L / 32) <= L / 2)
-  gp<double> ck = glob(reinterpret_cast<double*>(cpl));
+  gp<double> ck = glob(cpl);
   const uint32_t base = (uint32_t)c0 * (uint32_t)L;
   const int me = threadIdx.x;
   const bool owner = me < nl;

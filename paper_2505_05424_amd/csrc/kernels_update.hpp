@@ -56,6 +56,15 @@ __device__ __forceinline__ void cone_input(const Geo& g, const T* __restrict__ q
   }
 }
 
+// The arithmetic of the steps below is spelled with explicit fused and rounded
+// operations (no contraction left to the compiler), so that every kernel that
+// computes a step gives the same bits for it: the one-sweep iteration
+// (fuse_body) and the separate sweeps may follow each other in one solve.
+__device__ __forceinline__ double mul_rn(double a, double b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 // Projection onto the second-order cone {y0 >= |ybar|} (eq. app-proj), in
 // place, in double: y if |ybar| <= y0; 0 if |ybar| <= -y0; otherwise
 // 1/2 (y0 + |ybar|) (1; ybar/|ybar|).
@@ -76,7 +85,24 @@ __device__ __forceinline__ void soc_project(double (&y)[K]) {
   const double s = a / nrm;
   y[0] = a;
 #pragma unroll
-  for (int k = 1; k < K; ++k) y[k] *= s;
+  for (int k = 1; k < K; ++k) y[k] = mul_rn(y[k], s);
+}
+
+// The same without branches (the same bits), for sweeps whose other work hides
+// the division.
+template <int K>
+__device__ __forceinline__ void soc_project_select(double (&y)[K]) {
+  double n2 = 0.0;
+#pragma unroll
+  for (int k = 1; k < K; ++k) n2 = fma(y[k], y[k], n2);
+  const double nrm = sqrt(n2);
+  const double y0 = y[0];
+  const bool in = nrm <= y0, polar = !in && nrm <= -y0;
+  const double a = 0.5 * (y0 + nrm);
+  const double s = in ? 1.0 : a / nrm;
+  y[0] = in ? y0 : (polar ? 0.0 : a);
+#pragma unroll
+  for (int k = 1; k < K; ++k) y[k] = polar ? 0.0 : mul_rn(y[k], s);
 }
 
 // ---- node sweeps ------------------------------------------------------------
@@ -137,39 +163,72 @@ __device__ __forceinline__ void shift_fq(T (&a)[kMaxAxes][2], const T (&b)[kMaxA
 }
 
 // u = B_omega F q + d - beta/sigma at a cell from its beta values bt, q0 and
-// the F q values of slices t (fa) and t+1 (fb), in double.
+// the F q values of slices t (fa) and t+1 (fb), in double; p = beta/sigma.
 template <typename T, int D>
 __device__ __forceinline__ void cone_arg(const T (&bt)[4 * D + 2], double q0, const T (&fa)[kMaxAxes][2],
                                          const T (&fb)[kMaxAxes][2], double sw, double inv_sigma,
-                                         double (&u)[4 * D + 2]) {
+                                         double (&u)[4 * D + 2], double (&p)[4 * D + 2]) {
   constexpr int K = 4 * D + 2;
-  u[0] = 1.0 - q0 - (double)bt[0] * inv_sigma;
-  u[K - 1] = 1.0 + q0 - (double)bt[K - 1] * inv_sigma;
+#pragma unroll
+  for (int k = 0; k < K; ++k) p[k] = mul_rn((double)bt[k], inv_sigma);
+  u[0] = fma(-inv_sigma, (double)bt[0], 1.0 - q0);
+  u[K - 1] = fma(-inv_sigma, (double)bt[K - 1], 1.0 + q0);
 #pragma unroll
   for (int d = 1; d <= D; ++d) {
     const int k = 1 + 4 * (d - 1);
-    u[k + 0] = sw * (double)fa[d][0] - (double)bt[k + 0] * inv_sigma;
-    u[k + 1] = sw * (double)fa[d][1] - (double)bt[k + 1] * inv_sigma;
-    u[k + 2] = sw * (double)fb[d][0] - (double)bt[k + 2] * inv_sigma;
-    u[k + 3] = sw * (double)fb[d][1] - (double)bt[k + 3] * inv_sigma;
+    u[k + 0] = fma(sw, (double)fa[d][0], -p[k + 0]);
+    u[k + 1] = fma(sw, (double)fa[d][1], -p[k + 1]);
+    u[k + 2] = fma(sw, (double)fb[d][0], -p[k + 2]);
+    u[k + 3] = fma(sw, (double)fb[d][1], -p[k + 3]);
   }
 }
 
-// z-step output of one cell from its projected u = Pi(...) and the beta
-// values bt the argument was formed with: w = z - d + beta/sigma; the
-// weighted components sqrt(omega/2) w_{d,v} go to the W planes (for the q_d
-// update) and w_{K-1} - w_0 to the FP64 plane DW (for the q0 update: in the
-// storage type its rounding would enter every alpha0 increment, which near
-// convergence are smaller than that rounding).
+// The two outputs of a cell's z-step that the q-step reads, from its
+// projected u = Pi(...) and p = beta/sigma (w = z - d + p): the weighted
+// component sqrt(omega/2) w_k, and w_{K-1} - w_0.
+template <typename T>
+__device__ __forceinline__ T cone_w(double u, double p, double sw) {
+  return (T)mul_rn(sw, u + p);
+}
+template <int K>
+__device__ __forceinline__ double cone_dw(const double (&u)[K], const double (&p)[K]) {
+  const double w0 = (u[0] - 1.0) + p[0];
+  const double wl = (u[K - 1] - 1.0) + p[K - 1];
+  return wl - w0;
+}
+
+// q0 and alpha0 at a cell (d = 0: the diagonal of Prop. 3.2 is 3, here as its
+// reciprocal): dphi = phi(t+1) - phi(t), inv_h = n0, wsum = w_{K-1} - w_0.
+__device__ __forceinline__ double q0_new(double dphi, double inv_h, double a, double inv_sigma, double wsum) {
+  return mul_rn(fma(a, inv_sigma, mul_rn(dphi, inv_h)) + wsum, 1.0 / 3.0);
+}
+// q_d (d >= 1) from dphi = phi(x + e_d) - phi(x), alpha_d, the adjacent
+// cells' weighted w components and the diagonal. Of the two products one is
+// rounded by itself, in 1D the other than in 2D and 3D (mixed-precision
+// iterates depend on it bit by bit, and saved ones are continued).
+template <int D>
+__device__ __forceinline__ double qd_new(double dphi, double inv_h, double a, double inv_sigma, double acc,
+                                         double diag) {
+  const double s = D == 1 ? fma(inv_h, dphi, mul_rn(a, inv_sigma)) : fma(a, inv_sigma, mul_rn(dphi, inv_h));
+  return (s + acc) / diag;
+}
+// alpha += tau sigma (A phi - q_new), ts = tau sigma
+__device__ __forceinline__ double alpha_new(double a, double ts, double dphi, double inv_h, double qn) {
+  return fma(ts, fma(inv_h, dphi, -qn), a);
+}
+
+// z-step output of one cell from its projected u and p = beta/sigma: the
+// weighted components go to the W planes (for the q_d update) and
+// w_{K-1} - w_0 to the FP64 plane DW (for the q0 update: in the storage type
+// its rounding would enter every alpha0 increment, which near convergence are
+// smaller than that rounding).
 template <typename T, int D>
-__device__ __forceinline__ void cone_store(const double (&u)[4 * D + 2], const T (&bt)[4 * D + 2], double sw,
-                                           double inv_sigma, gp<T> W, gp<double> DW, uint32_t nb, uint32_t i) {
+__device__ __forceinline__ void cone_store(const double (&u)[4 * D + 2], const double (&p)[4 * D + 2], double sw,
+                                           gp<T> W, gp<double> DW, uint32_t nb, uint32_t i) {
   constexpr int K = 4 * D + 2;
-  const double w0 = u[0] - 1.0 + (double)bt[0] * inv_sigma;
-  const double wl = u[K - 1] - 1.0 + (double)bt[K - 1] * inv_sigma;
 #pragma unroll
-  for (int k = 1; k < K - 1; ++k) W[(size_t)(k - 1) * nb + i] = (T)(sw * (u[k] + (double)bt[k] * inv_sigma));
-  DW[i] = wl - w0;
+  for (int k = 1; k < K - 1; ++k) W[(size_t)(k - 1) * nb + i] = cone_w<T>(u[k], p[k], sw);
+  DW[i] = cone_dw<K>(u, p);
 }
 
 // a1 + a2 per cell (the z-step of Algorithm 2): z = Pi(u), then cone_store.
@@ -198,10 +257,10 @@ __device__ __forceinline__ void cone_body(const Geo& g, const T* __restrict__ q_
 #pragma unroll
     for (int k = 0; k < K; ++k) bt[k] = beta[(size_t)k * nb + i];
     const double q0 = (double)q[i];
-    double u[K];
-    cone_arg<T, D>(bt, q0, fa, fb, sw, inv_sigma, u);
+    double u[K], p[K];
+    cone_arg<T, D>(bt, q0, fa, fb, sw, inv_sigma, u, p);
     soc_project<K>(u);
-    cone_store<T, D>(u, bt, sw, inv_sigma, W, DW, nb, i);
+    cone_store<T, D>(u, p, sw, W, DW, nb, i);
     shift_fq<T, D>(fa, fb);
   }
 }
@@ -262,7 +321,7 @@ __device__ __forceinline__ void q_body(const Geo& g, const double* __restrict__ 
   gp<const double> DW = glob(DW_);
   gp<const double> om = glob(om_sp);
   const uint32_t nb = (uint32_t)g.nb, nx = (uint32_t)g.nx;
-  const double sigma = glob(ctl)->sigma, tau = glob(ctl)->tau, inv_sigma = 1.0 / sigma;
+  const double sigma = glob(ctl)->sigma, ts = glob(ctl)->tau * sigma, inv_sigma = 1.0 / sigma;
   double om_a = om[c.xs], om_b[kMaxAxes];
 #pragma unroll
   for (int d = 1; d <= D; ++d) om_b[d] = c.x[d] < g.n[d] ? om[c.xs + (uint32_t)g.stride[d]] : 0.0;
@@ -277,10 +336,10 @@ __device__ __forceinline__ void q_body(const Geo& g, const double* __restrict__ 
     const double ct = (double)has_now + (double)has_prev;
     if (has_now) {
       const double ph1 = more ? nxt.ph : phi[i + nx];
-      const double g0 = (ph1 - cur.ph) * g.inv_h[0];
-      const double q0n = (g0 + cur.a0 * inv_sigma + cur.dw) * (1.0 / 3.0);
+      const double dphi = ph1 - cur.ph;
+      const double q0n = q0_new(dphi, g.inv_h[0], cur.a0, inv_sigma, cur.dw);
       qn[i] = (T)q0n;
-      alpha[i] = cur.a0 + tau * sigma * (g0 - q0n);
+      alpha[i] = alpha_new(cur.a0, ts, dphi, g.inv_h[0], q0n);
     }
 #pragma unroll
     for (int d = 1; d <= D; ++d) {
@@ -288,12 +347,11 @@ __device__ __forceinline__ void q_body(const Geo& g, const double* __restrict__ 
       double acc = 0.0;
       if (has_now) acc += (double)cur.w[d][0] + (double)cur.w[d][1];
       if (has_prev) acc += (double)cur.w[d][2] + (double)cur.w[d][3];
-      const double diag = 1.0 + 0.5 * ct * (om_a + om_b[d]);
-      const double gd = (cur.phd[d] - cur.ph) * g.inv_h[d];
-      const double ad = cur.ad[d];
-      const double qdn = (gd + ad * inv_sigma + acc) / diag;
+      const double diag = fma(0.5 * ct, om_a + om_b[d], 1.0);
+      const double dphi = cur.phd[d] - cur.ph;
+      const double qdn = qd_new<D>(dphi, g.inv_h[d], cur.ad[d], inv_sigma, acc, diag);
       qn[(size_t)d * nb + i] = (T)qdn;
-      alpha[(size_t)d * nb + i] = ad + tau * sigma * (gd - qdn);
+      alpha[(size_t)d * nb + i] = alpha_new(cur.ad[d], ts, dphi, g.inv_h[d], qdn);
     }
     cur = nxt;
   }
@@ -305,6 +363,24 @@ __device__ __forceinline__ void q_body(const Geo& g, const double* __restrict__ 
 // FP64 phi (path-graph Laplacian / h_d^2 per axis, Neumann ends). The time
 // neighbours (q0 - alpha0/sigma at t-1, phi at t-1 and t) are carried, and
 // the loads of slice t+1 are issued before slice t is computed.
+// A^*A phi at node (t, x): the path-graph Laplacians / h_d^2 with Neumann ends.
+// phm, phn: phi at t - 1 and t + 1; phs[d]: phi at x - e_d and x + e_d.
+template <int D>
+__device__ __forceinline__ double neg_laplacian(const Geo& g, int t, const int (&x)[kMaxAxes], double ph, double phm,
+                                                double phn, const double (&phs)[kMaxAxes][2]) {
+  const double w0 = g.inv_h[0] * g.inv_h[0];
+  double r = 0.0;
+  if (t >= 1) r = fma(ph - phm, w0, r);
+  if (t < g.n[0]) r = fma(-w0, phn - ph, r);
+#pragma unroll
+  for (int d = 1; d <= D; ++d) {
+    const double wd = g.inv_h[d] * g.inv_h[d];
+    if (x[d] >= 1) r = fma(ph - phs[d][0], wd, r);
+    if (x[d] < g.n[d]) r = fma(-wd, phs[d][1] - ph, r);
+  }
+  return r;
+}
+
 template <typename T, int D>
 struct RhsSlice {
   T q0;                     // q0 at the cell t (t < n0)
@@ -356,11 +432,10 @@ __device__ __forceinline__ void rhs_body(const Geo& g, const T* __restrict__ q_,
   gp<T> out = glob(out_);
   const uint32_t nx = (uint32_t)g.nx, xs = c.xs;
   const int n0 = g.n[0];
-  const double w0 = g.inv_h[0] * g.inv_h[0];
   uint32_t i = (uint32_t)c.t0 * nx + xs;
   double y0m = 0.0, phm = 0.0, ph = 0.0;
   if (c.t0 >= 1) {
-    y0m = (double)q[i - nx] - al[i - nx] * inv_sigma;
+    y0m = fma(-inv_sigma, al[i - nx], (double)q[i - nx]);
     if (DEFECT) phm = phi[i - nx];
   }
   if (DEFECT) ph = phi[i];
@@ -369,29 +444,20 @@ __device__ __forceinline__ void rhs_body(const Geo& g, const T* __restrict__ q_,
   for (int t = c.t0; t < c.t1; ++t, i += nx) {
     if (t + 1 < c.t1) rhs_load<T, D, DEFECT>(g, c, t + 1, i + nx, q, al, phi, c_lo_, c_hi_, nxt);
     double b = 0.0;
-    if (t >= 1) b += y0m * g.inv_h[0];
+    if (t >= 1) b = fma(y0m, g.inv_h[0], b);
     double y0 = 0.0;
     if (t < n0) {
-      y0 = (double)cur.q0 - cur.a0 * inv_sigma;
-      b -= y0 * g.inv_h[0];
+      y0 = fma(-inv_sigma, cur.a0, (double)cur.q0);
+      b = fma(-g.inv_h[0], y0, b);
     }
 #pragma unroll
     for (int d = 1; d <= D; ++d) {
-      if (c.x[d] >= 1) b += ((double)cur.qd[d][0] - cur.ad[d][0] * inv_sigma) * g.inv_h[d];
-      if (c.x[d] < g.n[d]) b -= ((double)cur.qd[d][1] - cur.ad[d][1] * inv_sigma) * g.inv_h[d];
+      if (c.x[d] >= 1) b = fma(fma(-inv_sigma, cur.ad[d][0], (double)cur.qd[d][0]), g.inv_h[d], b);
+      if (c.x[d] < g.n[d]) b = fma(-g.inv_h[d], fma(-inv_sigma, cur.ad[d][1], (double)cur.qd[d][1]), b);
     }
-    if (t == 0 || t == n0) b -= cur.cb * inv_sigma;
+    if (t == 0 || t == n0) b = fma(-inv_sigma, cur.cb, b);
     if (DEFECT) {
-      double r = 0.0;
-      if (t >= 1) r += (ph - phm) * w0;
-      if (t < n0) r -= (cur.phn - ph) * w0;
-#pragma unroll
-      for (int d = 1; d <= D; ++d) {
-        const double wd = g.inv_h[d] * g.inv_h[d];
-        if (c.x[d] >= 1) r += (ph - cur.phs[d][0]) * wd;
-        if (c.x[d] < g.n[d]) r -= (cur.phs[d][1] - ph) * wd;
-      }
-      b -= r;
+      b -= neg_laplacian<D>(g, t, c.x, ph, phm, cur.phn, cur.phs);
       phm = ph;
       ph = cur.phn;
     }
@@ -451,34 +517,78 @@ __device__ __forceinline__ void block_slot11(double v, double* __restrict__ part
   }
 }
 
-// beta update of a5 at one cell: z = Pi(u) from the old q (q0o, F q values
-// fa / fb of slices t and t+1) and the old beta bt, then
-// beta += tau sigma (z - B F q_new - d) with the new q (q0n, ga / gb) into bn;
-// ssq accumulates |z - B F q_new - d|^2.
+// beta += tau sigma (z - B F q_new - d) of a5 for the components of one cell
+// that meet q at its first time node (0, K-1 and (d, 1), (d, 2)), from its
+// projected z = u, its old beta values bt, its new q0 and the new F q values
+// ga of that node, into bn; ts = tau sigma. Returns the sum of squares of
+// z - B F q_new - d over them.
 template <typename T, int D>
-__device__ __forceinline__ void beta_cell(const T (&bt)[4 * D + 2], double q0o, const T (&fa)[kMaxAxes][2],
-                                          const T (&fb)[kMaxAxes][2], double q0n, const T (&ga)[kMaxAxes][2],
-                                          const T (&gb)[kMaxAxes][2], double sw, double sigma, double tau,
-                                          double inv_sigma, double& ssq, T (&bn)[4 * D + 2]) {
+__device__ __forceinline__ double beta_first(const double (&u)[4 * D + 2], const T (&bt)[4 * D + 2], double q0n,
+                                             const T (&ga)[kMaxAxes][2], double sw, double ts,
+                                             T (&bn)[4 * D + 2]) {
   constexpr int K = 4 * D + 2;
-  double u[K];
-  cone_arg<T, D>(bt, q0o, fa, fb, sw, inv_sigma, u);
-  soc_project<K>(u);
-  auto upd = [&](int k, double bq) {
-    const double r = u[k] - bq;
-    ssq = fma(r, r, ssq);
-    bn[k] = (T)((double)bt[k] + tau * sigma * r);
-  };
-  upd(0, 1.0 - q0n);
+  const double r0 = u[0] - (1.0 - q0n), rl = u[K - 1] - (1.0 + q0n);
+  bn[0] = (T)fma(ts, r0, (double)bt[0]);
+  bn[K - 1] = (T)fma(ts, rl, (double)bt[K - 1]);
+  double ssq = fma(rl, rl, mul_rn(r0, r0));
 #pragma unroll
   for (int d = 1; d <= D; ++d) {
     const int k = 1 + 4 * (d - 1);
-    upd(k + 0, sw * (double)ga[d][0]);
-    upd(k + 1, sw * (double)ga[d][1]);
-    upd(k + 2, sw * (double)gb[d][0]);
-    upd(k + 3, sw * (double)gb[d][1]);
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const double r = fma(-sw, (double)ga[d][v], u[k + v]);
+      bn[k + v] = (T)fma(ts, r, (double)bt[k + v]);
+      ssq = fma(r, r, ssq);
+    }
   }
-  upd(K - 1, 1.0 + q0n);
+  return ssq;
+}
+
+// The components (d, 3) and (d, 4), which meet q at the second time node (gb);
+// z34 / b34: their z and old beta. Adds to the sum of squares.
+template <typename T, int D>
+__device__ __forceinline__ double beta_second(const double (&z34)[kMaxAxes][2], const T (&b34)[kMaxAxes][2],
+                                              const T (&gb)[kMaxAxes][2], double sw, double ts, double ssq,
+                                              T (&bn)[kMaxAxes][2]) {
+#pragma unroll
+  for (int d = 1; d <= D; ++d) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      const double r = fma(-sw, (double)gb[d][v], z34[d][v]);
+      bn[d][v] = (T)fma(ts, r, (double)b34[d][v]);
+      ssq = fma(r, r, ssq);
+    }
+  }
+  return ssq;
+}
+
+// The whole beta step of a cell with z = Pi(u) recomputed from the old q (q0o,
+// F q values fa / fb of slices t and t+1) and the old beta.
+template <typename T, int D>
+__device__ __forceinline__ double beta_cell(const T (&bt)[4 * D + 2], double q0o, const T (&fa)[kMaxAxes][2],
+                                            const T (&fb)[kMaxAxes][2], double q0n, const T (&ga)[kMaxAxes][2],
+                                            const T (&gb)[kMaxAxes][2], double sw, double ts, double inv_sigma,
+                                            T (&bn)[4 * D + 2]) {
+  double u[4 * D + 2], p[4 * D + 2], z34[kMaxAxes][2];
+  T b34[kMaxAxes][2], n34[kMaxAxes][2];
+  cone_arg<T, D>(bt, q0o, fa, fb, sw, inv_sigma, u, p);
+  soc_project<4 * D + 2>(u);
+#pragma unroll
+  for (int d = 1; d <= D; ++d) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+      z34[d][v] = u[4 * (d - 1) + 3 + v];
+      b34[d][v] = bt[4 * (d - 1) + 3 + v];
+    }
+  }
+  double ssq = beta_first<T, D>(u, bt, q0n, ga, sw, ts, bn);
+  ssq = beta_second<T, D>(z34, b34, gb, sw, ts, ssq, n34);
+#pragma unroll
+  for (int d = 1; d <= D; ++d) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) bn[4 * (d - 1) + 3 + v] = n34[d][v];
+  }
+  return ssq;
 }
 
 // beta update of a5 per cell (z recomputed from the old q and beta); at
@@ -491,7 +601,7 @@ __device__ __forceinline__ void beta_body(const Geo& g, const T* __restrict__ q_
   constexpr int K = 4 * D + 2;
   const Column c = column_of<D>(g, blk);
   const int tend = min(c.t1, g.n[0]);
-  const double sigma = glob(ctl)->sigma, tau = glob(ctl)->tau, inv_sigma = 1.0 / sigma;
+  const double sigma = glob(ctl)->sigma, ts = glob(ctl)->tau * sigma, inv_sigma = 1.0 / sigma;
   double ssq = 0.0;
   if (c.live && c.t0 < tend) {
     gp<const T> q = glob(q_);
@@ -509,7 +619,7 @@ __device__ __forceinline__ void beta_body(const Geo& g, const T* __restrict__ q_
       T bt[K], bn[K];
 #pragma unroll
       for (int k = 0; k < K; ++k) bt[k] = beta[(size_t)k * nb + i];
-      beta_cell<T, D>(bt, (double)q[i], fa, fb, (double)qn[i], ga, gb, sw, sigma, tau, inv_sigma, ssq, bn);
+      ssq += beta_cell<T, D>(bt, (double)q[i], fa, fb, (double)qn[i], ga, gb, sw, ts, inv_sigma, bn);
 #pragma unroll
       for (int k = 0; k < K; ++k) beta[(size_t)k * nb + i] = bn[k];
       shift_fq<T, D>(fa, fb);
@@ -534,7 +644,7 @@ __device__ __forceinline__ void beta_cone_body(const Geo& g, const T* __restrict
   constexpr int K = 4 * D + 2;
   const Column c = column_of<D>(g, blk);
   const int tend = min(c.t1, g.n[0]);
-  const double sigma = glob(ctl)->sigma, tau = glob(ctl)->tau, inv_sigma = 1.0 / sigma;
+  const double sigma = glob(ctl)->sigma, ts = glob(ctl)->tau * sigma, inv_sigma = 1.0 / sigma;
   if (c.live && c.t0 < tend) {
     gp<const T> q = glob(q_);
     gp<const T> qn = glob(qn_);
@@ -547,7 +657,6 @@ __device__ __forceinline__ void beta_cone_body(const Geo& g, const T* __restrict
     T fa[kMaxAxes][2], fb[kMaxAxes][2], ga[kMaxAxes][2], gb[kMaxAxes][2];
     load_fq<T, D>(g, q, i, c, fa);
     load_fq<T, D>(g, qn, i, c, ga);
-    double ssq = 0.0;
     for (int t = c.t0; t < tend; ++t, i += nx) {
       load_fq<T, D>(g, q, i + nx, c, fb);
       load_fq<T, D>(g, qn, i + nx, c, gb);
@@ -555,18 +664,30 @@ __device__ __forceinline__ void beta_cone_body(const Geo& g, const T* __restrict
 #pragma unroll
       for (int k = 0; k < K; ++k) bt[k] = beta[(size_t)k * nb + i];
       const double q0n = (double)qn[i];
-      beta_cell<T, D>(bt, (double)q[i], fa, fb, q0n, ga, gb, sw, sigma, tau, inv_sigma, ssq, bn);
+      (void)beta_cell<T, D>(bt, (double)q[i], fa, fb, q0n, ga, gb, sw, ts, inv_sigma, bn);
 #pragma unroll
       for (int k = 0; k < K; ++k) beta[(size_t)k * nb + i] = bn[k];
-      double u[K];
-      cone_arg<T, D>(bn, q0n, ga, gb, sw, inv_sigma, u);
+      double u[K], p[K];
+      cone_arg<T, D>(bn, q0n, ga, gb, sw, inv_sigma, u, p);
       soc_project<K>(u);
-      cone_store<T, D>(u, bn, sw, inv_sigma, W, DW, nb, i);
+      cone_store<T, D>(u, p, sw, W, DW, nb, i);
       shift_fq<T, D>(fa, fb);
       shift_fq<T, D>(ga, gb);
     }
   }
   if (blk == 0 && threadIdx.x == 0) glob(ctl)->iter += 1;
+}
+
+// The K planes of beta in one of its two places: components 0..4D-1 from lo,
+// the last two from hi.
+template <typename T>
+struct BetaPlanes {
+  T* lo;
+  T* hi;
+};
+template <typename T, int D>
+__device__ __forceinline__ gp<T> beta_plane(const BetaPlanes<T>& b, int k, uint32_t nb) {
+  return k < 4 * D ? glob(b.lo) + (size_t)k * nb : glob(b.hi) + (size_t)(k - 4 * D) * nb;
 }
 
 // Partial sums for the residuals of Sec. 5.3 at (phi, q, alpha, beta), one
@@ -596,7 +717,7 @@ struct ResSlice {
 
 template <typename T, int D>
 __device__ __forceinline__ void res_load(const Geo& g, const Column& c, int t, uint32_t i, gp<const double> phi,
-                                         gp<const T> q, gp<const double> alpha, gp<const T> beta,
+                                         gp<const T> q, gp<const double> alpha, const BetaPlanes<T>& beta,
                                          const double* c_lo, const double* c_hi, ResSlice<T, D>& s) {
   constexpr int K = 4 * D + 2;
   const uint32_t nb = (uint32_t)g.nb, nx = (uint32_t)g.nx;
@@ -606,8 +727,8 @@ __device__ __forceinline__ void res_load(const Geo& g, const Column& c, int t, u
   s.cc = t == 0 ? glob(c_lo)[c.xs] : (t == n0 ? glob(c_hi)[c.xs] : 0.0);
   s.ph1 = cell ? phi[i + nx] : 0.0;
   s.q0 = cell ? q[i] : T(0);
-  s.bK = cell ? beta[(size_t)(K - 1) * nb + i] : T(0);
-  s.b0 = cell ? beta[i] : T(0);
+  s.bK = cell ? beta_plane<T, D>(beta, K - 1, nb)[i] : T(0);
+  s.b0 = cell ? beta_plane<T, D>(beta, 0, nb)[i] : T(0);
 #pragma unroll
   for (int d = 1; d <= D; ++d) {
     const uint32_t sd = (uint32_t)g.stride[d];
@@ -620,19 +741,19 @@ __device__ __forceinline__ void res_load(const Geo& g, const Column& c, int t, u
     s.phd[d] = hi ? phi[i + sd] : 0.0;
     s.fq1[d][0] = cell && lo ? qd[i + nx - sd] : T(0);
     s.fq1[d][1] = cell && hi ? qd[i + nx] : T(0);
-    s.b01[d][0] = cell && hi ? beta[(size_t)(k + 0) * nb + i + sd] : T(0);
-    s.b01[d][1] = cell && hi ? beta[(size_t)(k + 1) * nb + i] : T(0);
-    s.b23[d][0] = cell && hi ? beta[(size_t)(k + 2) * nb + i + sd] : T(0);
-    s.b23[d][1] = cell && hi ? beta[(size_t)(k + 3) * nb + i] : T(0);
+    s.b01[d][0] = cell && hi ? beta_plane<T, D>(beta, k + 0, nb)[i + sd] : T(0);
+    s.b01[d][1] = cell && hi ? beta_plane<T, D>(beta, k + 1, nb)[i] : T(0);
+    s.b23[d][0] = cell && hi ? beta_plane<T, D>(beta, k + 2, nb)[i + sd] : T(0);
+    s.b23[d][1] = cell && hi ? beta_plane<T, D>(beta, k + 3, nb)[i] : T(0);
     s.a0s[d] = cell && hi ? alpha[i + sd] : 0.0;
   }
 }
 
-template <typename T, int D>
+template <typename T, int D, bool SSQ>
 __device__ __forceinline__ void resid_body(const Geo& g, const double* phi_, const T* q_, const double* alpha_,
-                                           const T* beta_, const double* om_sp, const double* sw_sp,
-                                           const double* c_lo_, const double* c_hi_, double* __restrict__ partials,
-                                           uint32_t blk) {
+                                           const BetaPlanes<T>& beta, const double* om_sp, const double* sw_sp,
+                                           const double* c_lo_, const double* c_hi_, const double* ssq_,
+                                           double* __restrict__ partials, uint32_t blk) {
   double s[kNumSums];
 #pragma unroll
   for (int k = 0; k < kNumSums; ++k) s[k] = 0.0;
@@ -641,7 +762,6 @@ __device__ __forceinline__ void resid_body(const Geo& g, const double* phi_, con
     gp<const double> phi = glob(phi_);
     gp<const T> q = glob(q_);
     gp<const double> alpha = glob(alpha_);
-    gp<const T> beta = glob(beta_);
     gp<const double> om = glob(om_sp);
     gp<const double> swp = glob(sw_sp);
     const uint32_t nb = (uint32_t)g.nb, nx = (uint32_t)g.nx, xs = c.xs;
@@ -669,8 +789,8 @@ __device__ __forceinline__ void resid_body(const Geo& g, const double* phi_, con
       fq0[d][0] = lo ? qd[i - sd] : T(0);
       fq0[d][1] = hi ? qd[i] : T(0);
       const bool prev = c.t0 >= 1 && hi;
-      b23p[d][0] = prev ? beta[(size_t)(k + 2) * nb + i - nx + sd] : T(0);
-      b23p[d][1] = prev ? beta[(size_t)(k + 3) * nb + i - nx] : T(0);
+      b23p[d][0] = prev ? beta_plane<T, D>(beta, k + 2, nb)[i - nx + sd] : T(0);
+      b23p[d][1] = prev ? beta_plane<T, D>(beta, k + 3, nb)[i - nx] : T(0);
       a0sp[d] = prev ? alpha[i - nx + sd] : 0.0;
     }
     if (c.t0 >= 1) a0p = alpha[i - nx];
@@ -691,6 +811,8 @@ __device__ __forceinline__ void resid_body(const Geo& g, const double* phi_, con
       s[3] += div * div;
       s[16] += cur.cc * ph;
       if (t < n0) {
+        // the cells' sums of the one-sweep iteration, in beta_body's order
+        if (SSQ) s[11] += glob(ssq_)[i];
         // q0, alpha0 at the cell
         const double g0 = (cur.ph1 - ph) * g.inv_h[0];
         const double q0 = (double)cur.q0, a0 = cur.a0;
@@ -763,7 +885,7 @@ __device__ __forceinline__ void resid_body(const Geo& g, const double* phi_, con
       cur = nxt;
     }
   }
-  block_partials<kNumSums>(s, partials, blk, g.nsweep, 11);
+  block_partials<kNumSums>(s, partials, blk, g.nsweep, SSQ ? -1 : 11);
 }
 
 // Scalars the finalize step needs besides the partials.
