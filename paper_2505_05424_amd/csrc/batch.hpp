@@ -10,6 +10,7 @@
 #include "geometry.hpp"
 #include "kernels_dct.hpp"
 #include "kernels_fused.hpp"
+#include "kernels_plane.hpp"
 #include "kernels_update.hpp"
 
 namespace dot {
@@ -47,6 +48,7 @@ struct Inst {
   double* ckpt;              // c' checkpoints of the one-lane elimination (W plane 0 without it)
   FuseGeo fg;
   uint32_t fblk0;            // first block in the fused grid
+  uint32_t plane0;           // first block in the plane-solve grid
 };
 
 // Instance of logical block L: map[L], or 0 without a map (an executor of
@@ -221,6 +223,17 @@ kb_axis_pass(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, in
   pa.ncols = s.g.nb / s.g.N[axis];
   axis_pass_body<T, D, KIND, SRC, DST, CW>(s.g, pa, s.tab[axis], SRC == kSrcAlt ? s.rhs2 : nullptr, s.work, s.phi,
                                            s.lam_other, s.lam_last, (int64_t)(L - s.tile0[axis]));
+}
+
+// One plane of the last two axes per workgroup (kernels_plane.hpp).
+template <typename T, int D, int SRC, int DST, int KS>
+__global__ void __launch_bounds__(kPlaneThreads)
+kb_plane(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map) {
+  const uint32_t L = xcd_remap(blockIdx.x, gridDim.x);
+  const Inst<T>& s = I[inst_of_block(map, L)];
+  if (stopped(s)) return;
+  plane_body<T, D, SRC, DST, KS>(s.g, s.tab[D - 1], s.tab[D], SRC == kSrcAlt ? s.rhs2 : nullptr, s.work, s.phi,
+                                 s.lam_other, s.lam_last, L - s.plane0);
 }
 
 // Last-axis tridiagonal solve over the tiles of the last-axis grid (CW lines

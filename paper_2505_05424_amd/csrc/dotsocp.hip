@@ -31,6 +31,7 @@
 #include "geometry.hpp"
 #include "kernels_dct.hpp"
 #include "kernels_multilevel.hpp"
+#include "kernels_plane.hpp"
 #include "kernels_update.hpp"
 
 using namespace dot;
@@ -162,6 +163,11 @@ void drop_graph(GraphCache& g) {
 struct Sched {
   int cw[kMaxAxes] = {0, 0, 0, 0};
   int waves[kMaxAxes] = {0, 0, 0, 0};
+  bool rule() const {    // nothing set: every launch follows the rules
+    for (int a = 0; a < kMaxAxes; ++a)
+      if (cw[a] || waves[a]) return false;
+    return true;
+  }
   bool tuned = false;   // set by the autotuner (measured), not by the rule or the caller
   int candidates = 0;   // schedules the autotuner timed
   double us = 0.0;      // one transform sequence with this schedule (autotuner), us
@@ -316,6 +322,18 @@ int build_axis(dot_plan* P, int a, void** buf, AxisTab<T>* tab) {
   all.insert(all.end(), fo.begin(), fo.end());
   all.insert(all.end(), ie.begin(), ie.end());
   all.insert(all.end(), io.begin(), io.end());
+  size_t lane_at[4] = {0, 0, 0, 0};
+  const bool lanes = L <= kPlaneAxis;
+  if (lanes) {
+    const std::vector<T>* frag[4] = {&fe, &fo, &ie, &io};
+    for (int i = 0; i < 4; ++i) {
+      const int n = i % 2 ? no : ne, rb = (n + 15) / 16, kr = (n + 3) / 4, nch = ksteps(n) / kU + 1;
+      lane_at[i] = all.size();
+      for (int m = 0; m < rb; ++m)
+        for (int s = 0; s < kr; ++s)
+          for (int l = 0; l < 64; ++l) all.push_back((*frag[i])[(((size_t)m * nch + s / kU) * 64 + l) * kU + s % kU]);
+    }
+  }
   T* d = nullptr;
   int rc = upload(&d, all);
   if (rc) return rc;
@@ -324,6 +342,7 @@ int build_axis(dot_plan* P, int a, void** buf, AxisTab<T>* tab) {
   tab->fo = d + fe.size();
   tab->ie = d + fe.size() + fo.size();
   tab->io = d + fe.size() + fo.size() + ie.size();
+  for (int i = 0; i < 4; ++i) tab->pl[i] = lanes ? d + lane_at[i] : nullptr;
   tab->L = L;
   tab->M = M;
   tab->ne = ne;
@@ -444,6 +463,49 @@ AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
   }
   ag.waves = s.waves[a] ? s.waves[a] : waves;
   return ag;
+}
+
+// Launch of the plane solve over the instances plans[0..count); steps = 0
+// where the passes run: an axis of more than 72 points, two of more than 64
+// that leave a wave more line blocks than it holds, a last axis that is
+// eliminated, a schedule that was set (it names passes), or no gain. The rule
+// (us per iteration, passes -> plane solve): the launches that it saves are
+// all there is to gain, so it holds while the planes are solved in at most two
+// rounds over the CUs (FP64 400x20^2 107.3 -> 102.0, 20^4 71.5 -> 66.8, 1D
+// 16x32 23.7 -> 17.3; 12x40x27x31, 533 planes, 116.1 -> 116.8, 900x15^2 217.9
+// -> 221.8; mixed 85.0 -> 77.0, 62.5 -> 55.3, 23.8 -> 16.9, 90.8 -> 87.0, 184.7
+// -> 182.6) and, in FP64, up to 4096 points, past which a wave takes a second
+// line block (32x63^2 47.7 -> 45.5, 64x32x64 51.4 -> 47.8, but 32x64^2 51.4 ->
+// 54.6; mixed 43.7 -> 38.2, 44.9 -> 38.8, 46.2 -> 43.4).
+constexpr int64_t kPlaneCount = 512;
+constexpr int kPlanePoints64 = 4096;
+struct PlaneGeom {
+  int steps = 0;
+  int64_t blocks = 0;
+  size_t smem = 0;
+};
+int64_t plane_count(const dot_plan* P) { return P->g.nb / ((int64_t)P->g.N[P->D - 1] * P->g.N[P->D]); }
+PlaneGeom plane_geom(dot_plan* const* plans, int count, const Sched& s) {
+  PlaneGeom pg;
+  if (!s.rule()) return pg;
+  int longest = 0;
+  for (int i = 0; i < count; ++i) {
+    const dot_plan* P = plans[i];
+    const int N1 = P->g.N[P->D - 1], N2 = P->g.N[P->D];
+    if (P->tri || std::max(N1, N2) > kPlaneAxis) return PlaneGeom();
+    if (P->precision == DOT_FP64 && N1 * N2 > kPlanePoints64) return PlaneGeom();
+    longest = std::max({longest, N1, N2});
+    const int row = P->precision == DOT_FP64 ? plane_stride<double>(N2) : plane_stride<float>(N2);
+    pg.smem = std::max(pg.smem, ((size_t)N1 * row + N1 + N2) * P->scalar_bytes);
+    pg.blocks += plane_count(P);
+  }
+  if (pg.blocks > kPlaneCount) return PlaneGeom();
+  pg.steps = longest > 64 ? 9 : 8;
+  for (int i = 0; i < count; ++i) {
+    const int N1 = plans[i]->g.N[plans[i]->D - 1], N2 = plans[i]->g.N[plans[i]->D];
+    if (plane_blocks(N1, N2) > plane_items(pg.steps) || plane_blocks(N2, N1) > plane_items(pg.steps)) return PlaneGeom();
+  }
+  return pg;
 }
 
 // Schedules of axis a that every instance of a launch can take: the tile
@@ -793,6 +855,10 @@ struct Exec {
   int ntri = 0;       // instances whose last axis takes the tridiagonal solve
   int ntri_long = 0;  // of those, lines longer than the partitioned solve takes
   int64_t nodes = 0;  // grid nodes over all instances
+  int plane_steps = 0;  // plane solve of the last two axes (0: passes)
+  const uint16_t* map_plane = nullptr;
+  unsigned grid_plane = 0;
+  size_t smem_plane = 0;
   bool fused = false;  // one-sweep iterations (descriptors carry fuse_fields)
   const uint16_t* map_fuse = nullptr;
   unsigned grid_fuse = 0;
@@ -866,6 +932,20 @@ int launch_tri(const Exec& E, hipStream_t st) {
   }
 }
 
+template <typename T, int D, int SRC, int DST, int KS>
+int launch_plane_ks(const Exec& E, hipStream_t st) {
+  auto fn = kb_plane<T, D, SRC, DST, KS>;
+  hipLaunchKernelGGL(fn, dim3(E.grid_plane), dim3(kPlaneThreads), E.smem_plane, st, (const Inst<T>*)E.d_inst,
+                     E.map_plane);
+  HIP_OK(hipGetLastError());
+  return DOT_OK;
+}
+
+template <typename T, int D, int SRC, int DST>
+int launch_plane(const Exec& E, hipStream_t st) {
+  return E.plane_steps == 8 ? launch_plane_ks<T, D, SRC, DST, 8>(E, st) : launch_plane_ks<T, D, SRC, DST, 9>(E, st);
+}
+
 // The 2D+1 transform passes of one Poisson solve (a3 + a4): first pass on the
 // time axis loads according to SRC, forward passes on the middle axes, the
 // fused forward/scale/inverse pass on the last axis (or, for instances with
@@ -874,6 +954,20 @@ int launch_tri(const Exec& E, hipStream_t st) {
 template <typename T, int D, int SRC, int DST>
 int run_passes(const Exec& E, int par, double sigma, hipStream_t st) {
   int rc;
+  if (E.plane_steps && !(E.prof && E.prof->cls >= 0)) {
+    // the last two axes in one launch (kernel classes timed one by one run as passes)
+    if constexpr (D == 1) {
+      return launch_plane<T, D, SRC, DST>(E, st);
+    } else {
+      if ((rc = launch_pass<T, D, kFwd, SRC, kDstPlane>(E, 0, par, sigma, st))) return rc;
+      for (int a = 1; a < D - 1; ++a)
+        if ((rc = launch_pass<T, D, kFwd, kSrcPlane, kDstPlane>(E, a, par, sigma, st))) return rc;
+      if ((rc = launch_plane<T, D, kSrcPlane, kDstPlane>(E, st))) return rc;
+      for (int a = D - 2; a >= 1; --a)
+        if ((rc = launch_pass<T, D, kInv, kSrcPlane, kDstPlane>(E, a, par, sigma, st))) return rc;
+      return launch_pass<T, D, kInv, kSrcPlane, DST>(E, 0, par, sigma, st);
+    }
+  }
   if ((rc = launch_pass<T, D, kFwd, SRC, kDstPlane>(E, 0, par, sigma, st))) return rc;
   for (int a = 1; a < D; ++a)
     if ((rc = launch_pass<T, D, kFwd, kSrcPlane, kDstPlane>(E, a, par, sigma, st))) return rc;
@@ -1362,6 +1456,13 @@ int dispatch(int precision, int D, A&&... args) {
 
 size_t inst_slot_bytes() { return align256(std::max(sizeof(Inst<double>), sizeof(Inst<float>))); }
 
+void set_plane(Exec& E, const PlaneGeom& pg, const uint16_t* map) {
+  E.plane_steps = pg.steps;
+  E.map_plane = map;
+  E.grid_plane = (unsigned)pg.blocks;
+  E.smem_plane = pg.smem;
+}
+
 // Single-instance executor of a plan; descriptor slot 0 (run) or 1 (steps).
 Exec plan_exec(dot_plan* P, int slot) {
   Exec E;
@@ -1386,6 +1487,7 @@ Exec plan_exec(dot_plan* P, int slot) {
     E.smem_axis[a] = ag.smem;
     E.waves_axis[a] = ag.waves;
   }
+  set_plane(E, plane_geom(&P, 1, P->sched), nullptr);
   E.fused = slot == 0 && P->fuse_ws && P->fg.nblk;
   E.grid_fuse = P->fg.nblk;
   E.lanes_fuse = fuse_waves(P->fg) * 64;
@@ -1740,6 +1842,10 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
     for (int k = 0; k < n; ++k)
       maps.insert(maps.end(), (size_t)tiles_for(plans[k]->lines[a], ag[a].cw), (uint16_t)idx[k]);
   }
+  const size_t plane_off = maps.size();
+  const PlaneGeom pg = plane_geom(plans.data(), n, s);
+  if (pg.steps)
+    for (int k = 0; k < n; ++k) maps.insert(maps.end(), (size_t)plane_count(plans[k]), (uint16_t)idx[k]);
   const size_t fuse_off = maps.size();
   int64_t all_nodes = 0;
   for (dot_plan* P : plans) all_nodes += P->g.nb;
@@ -1781,6 +1887,7 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
     E.nstaged += P->nblocks >= kFinStageMinRows ? 1 : 0;
     E.nodes += P->g.nb;
   }
+  set_plane(E, pg, B->d_maps + plane_off);
   B->fg = std::move(fg);
   E.map_fuse = B->d_maps + fuse_off;
   E.grid_fuse = (unsigned)fuse_blocks;
@@ -1823,7 +1930,7 @@ int batch_descriptors(dot_batch* B, void* ws, hipStream_t st) {
   std::vector<Inst<T>> host(count);
   B->E.fused = B->fuse_ws && B->E.grid_fuse;
   size_t fuse_off = 0;
-  uint32_t blk = 0, fblk = 0;
+  uint32_t blk = 0, fblk = 0, plane = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
   for (int i = 0; i < count; ++i) {
     dot_plan* P = B->plans[i];
@@ -1833,6 +1940,8 @@ int batch_descriptors(dot_batch* B, void* ws, hipStream_t st) {
     blk += (uint32_t)P->nblocks;
     host[i].fblk0 = fblk;
     fblk += B->fg[i].nblk;
+    host[i].plane0 = plane;
+    plane += (uint32_t)plane_count(P);
     for (int a = 0; a <= B->D; ++a) {
       host[i].tile0[a] = tile[a];
       tile[a] += (uint32_t)tiles_for(P->lines[a], B->E.cw_axis[a]);
@@ -2030,11 +2139,14 @@ int tune_schedule(Apply&& apply, const std::vector<std::vector<std::pair<int, in
   int rc = apply(rule, &E);
   double t_best = 0.0;
   if (rc || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t_best))) return rc;
-  Sched rule_x;  // the rule's schedule written out
+  Sched rule_x;  // the rule's schedule of the passes written out
   for (int a = 0; a <= D; ++a) {
     rule_x.cw[a] = E.cw_axis[a];
     rule_x.waves[a] = E.waves_axis[a];
   }
+  const Sched first = E.plane_steps ? rule : rule_x;  // what runs without a schedule
+  if (E.plane_steps && ((rc = apply(rule_x, &E)) || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t_best))))
+    return rc;
   Sched best = rule_x;
   int n = 1;
   for (int a = 0; a <= D; ++a) {
@@ -2055,13 +2167,13 @@ int tune_schedule(Apply&& apply, const std::vector<std::vector<std::pair<int, in
   double t_rule = 1e300, t_tuned = 1e300;
   for (int k = 0; k < 2; ++k) {
     double t = 0.0;
-    if ((rc = apply(rule_x, &E)) || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t))) return rc;
+    if ((rc = apply(first, &E)) || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t))) return rc;
     t_rule = std::min(t_rule, t);
     if ((rc = apply(best, &E)) || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t))) return rc;
     t_tuned = std::min(t_tuned, t);
   }
   if (!(t_tuned < t_rule)) {
-    best = rule_x;
+    best = first;
     t_tuned = t_rule;
   }
   best.tuned = true;
@@ -3260,7 +3372,8 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
                                            : choose_cw(all_lines, wide_ok, mid_ok);
   }
   // descriptors of the active instances, in slot order
-  uint32_t blk = 0;
+  const PlaneGeom pg = plane_geom(act.data(), (int)act.size(), Sched());
+  uint32_t blk = 0, plane = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
   int idx = 0;
   for (int sl = 0; sl < C->max_slots; ++sl) {
@@ -3271,6 +3384,8 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
     Inst<T> s = state_inst<T>(P, static_cast<char*>(C->arena_mem) + r->off, ctl);
     s.blk0 = blk;
     blk += (uint32_t)P->nblocks;
+    s.plane0 = plane;
+    plane += (uint32_t)plane_count(P);
     for (int a = 0; a <= C->D; ++a) {
       s.tile0[a] = tile[a];
       tile[a] += (uint32_t)tiles_for(P->lines[a], E.cw_axis[a]);
@@ -3310,6 +3425,9 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
     E.smem_axis[a] = smem;
     E.waves_axis[a] = waves;
   }
+  const size_t plane_off = maps.size();
+  if (pg.steps)
+    for (size_t k = 0; k < act.size(); ++k) maps.insert(maps.end(), (size_t)plane_count(act[k]), (uint16_t)k);
   if (host.size() * sizeof(Inst<T>) > C->d_inst_cap) {
     (void)hipFree(C->d_inst);
     C->d_inst_cap = host.size() * sizeof(Inst<T>) * 2;
@@ -3325,6 +3443,7 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   HIP_OK(hipStreamSynchronize(st));
   E.d_inst = C->d_inst;
   E.map_nodes = C->d_maps;
+  set_plane(E, pg, C->d_maps + plane_off);
   for (int a = 0; a <= C->D; ++a) E.map_axis[a] = C->d_maps + map_off[a];
   C->dirty = false;
   return DOT_OK;
