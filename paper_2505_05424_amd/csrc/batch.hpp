@@ -46,9 +46,11 @@ struct Inst {
   T* rhs2;
   double* ssq;
   double* ckpt;              // c' checkpoints of the one-lane elimination (W plane 0 without it)
+  const double* piv;         // pivots of the last axis's lines (plans with few long lines)
   FuseGeo fg;
   uint32_t fblk0;            // first block in the fused grid
   uint32_t plane0;           // first block in the plane-solve grid
+  uint32_t line0;            // first block in the long-line grid
 };
 
 // Instance of logical block L: map[L], or 0 without a map (an executor of
@@ -247,6 +249,23 @@ kb_tri_pass(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map) {
   const Inst<T>& s = I[inst_of_block(map, L)];
   if (stopped(s) || !s.tri || s.g.N[D] <= kTriPartMaxNodes) return;  // shorter lines: kb_tri_part
   tri_pass_body<T, CW>(s.g, s.work, s.ckpt, s.lam_other, (int64_t)(L - s.tile0[D]));
+}
+
+// The same where the launch has few long lines (tri_line_body), cw lines per
+// workgroup of a grid of its own, and the pivots that it reads.
+template <typename T, int D>
+__global__ void __launch_bounds__(kTriThreads)
+kb_tri_line(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int cw) {
+  const uint32_t L = xcd_remap(blockIdx.x, gridDim.x);
+  const Inst<T>& s = I[inst_of_block(map, L)];
+  if (stopped(s)) return;
+  tri_line_body<T>(s.g, s.work, s.piv, s.lam_other, (int64_t)(L - s.line0), cw);
+}
+template <typename T>
+__global__ void __launch_bounds__(64)
+kb_tri_pivots(Geo g, const T* __restrict__ lam_other, double* __restrict__ piv) {
+  const int64_t line = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  if (line < g.nb / g.N[g.D]) tri_pivots<T>(g, lam_other, piv, line);
 }
 
 // Partitioned last-axis solve (lines of up to kTriPartMaxNodes nodes) over the

@@ -193,6 +193,7 @@ struct dot_plan {
   bool wide_ok[kMaxAxes] = {true, true, true, true};  // the axis fits a tile of kCW lines
   bool mid_ok[kMaxAxes] = {true, true, true, true};   // a tile of kCWMid lines fits in kMidLds
   bool tri = false;      // the last axis is solved by tridiagonal elimination
+  double* piv = nullptr;    // pivots of the last axis's lines, where line_pays
   void* step_cbuf = nullptr;  // c' plane of the tridiagonal solve for step-level calls
   Sched sched;                // transform schedule of this plan's own launches
   // device constant tables
@@ -508,6 +509,66 @@ PlaneGeom plane_geom(dot_plan* const* plans, int count, const Sched& s) {
   return pg;
 }
 
+// Launch of the long-line solve over the instances plans[0..count) that have
+// lines longer than the partitioned solve takes; cw = 0 where there are none or
+// the chunked one-lane solve runs: a schedule was set (it names that one), or
+// the lines take more than two rounds over the CUs. The chain along a line is
+// the time of a round, whatever the line count; the chunked solve's is five
+// times as long but is one for 16384 lines (us per iteration, chunked -> whole,
+// FP64: 1D 64x1000 222.5 -> 61.5, 16x600 136.3 -> 43.1, 64x4000 811.7 -> 178.0;
+// 2D 16x40x700 204.9 -> 97.5, two rounds 30x130x1000 616.7 -> 530.6 and
+// 64x100x700 580.9 -> 543.3, three 64x200x600 919.4 -> 986.2; mixed 204.9 ->
+// 60.1, 124.9 -> 43.2, 742.7 -> 173.4, 194.6 -> 93.5, 513.8 -> 439.7, 470.0 ->
+// 441.2, 678.5 -> 754.2).
+constexpr int64_t kLineBlocks = 512;
+int line_cw(int64_t lines, size_t row) {
+  return (int)std::min<int64_t>({(lines + 255) / 256, kTriLineMax, (int64_t)(kTriLineLds / row)});
+}
+bool line_pays(int64_t lines, int L) {
+  const int cw = line_cw(lines, tri_line_bytes(L));
+  return cw > 0 && tiles_for(lines, cw) <= kLineBlocks;
+}
+bool line_long(const dot_plan* P) { return P->tri && P->g.N[P->D] > kTriPartMaxNodes; }
+struct LineGeom {
+  int cw = 0, insts = 0;
+  int64_t blocks = 0;
+  size_t smem = 0;
+};
+LineGeom line_geom(dot_plan* const* plans, int count, const Sched& s) {
+  LineGeom lg;
+  int64_t lines = 0;
+  size_t row = 0;
+  for (int i = 0; i < count; ++i) {
+    const dot_plan* P = plans[i];
+    if (!line_long(P)) continue;
+    if (!P->piv || !s.rule()) return LineGeom();
+    ++lg.insts;
+    lines += P->lines[P->D];
+    row = std::max(row, tri_line_bytes(P->g.N[P->D]));
+  }
+  if (!lg.insts) return lg;
+  lg.cw = line_cw(lines, row);
+  lg.smem = lg.cw * row + kTriLineMax * sizeof(double);
+  for (int i = 0; i < count; ++i)
+    if (line_long(plans[i])) lg.blocks += tiles_for(plans[i]->lines[plans[i]->D], lg.cw);
+  return lg.blocks <= kLineBlocks ? lg : LineGeom();
+}
+// The pivots of a plan. Without the memory for them the chunked solve runs.
+template <typename T>
+int build_pivots(dot_plan* P) {
+  const int64_t lines = P->g.nb / P->g.N[P->D];
+  if (hipMalloc((void**)&P->piv, (size_t)P->g.nb * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
+    P->piv = nullptr;
+    return DOT_OK;
+  }
+  hipLaunchKernelGGL((kb_tri_pivots<T>), dim3((unsigned)((lines + 63) / 64)), dim3(64), 0, nullptr, P->g,
+                     (const T*)P->lam_other, P->piv);
+  HIP_OK(hipGetLastError());
+  HIP_OK(hipStreamSynchronize(nullptr));
+  return DOT_OK;
+}
+
 // Schedules of axis a that every instance of a launch can take: the tile
 // widths its LDS and waves hold (the wide one only where the rule may pick
 // it; the tridiagonal-only last axis keeps its tile) and, per width, the wave
@@ -796,6 +857,7 @@ Inst<T> inst_of(const dot_plan* P, double* phi, T* scr, T* q, T* qn, double* alp
   for (int a = 0; a < kMaxAxes; ++a) s.tab[a] = tab_of<T>(P, a);
   s.fa = fin_args(P);
   s.ckpt = reinterpret_cast<double*>(W);
+  s.piv = P->piv;
   s.tri = P->tri;
   return s;
 }
@@ -853,7 +915,12 @@ struct Exec {
   int waves_axis[kMaxAxes] = {0, 0, 0, 0};
   int cw_axis[kMaxAxes] = {kCW, kCW, kCW, kCW};  // transform tile width per axis
   int ntri = 0;       // instances whose last axis takes the tridiagonal solve
-  int ntri_long = 0;  // of those, lines longer than the partitioned solve takes
+  int ntri_line = 0;  // of those, in the long-line solve
+  int ntri_long = 0;  // of those, in the chunked one-lane solve
+  int cw_line = 0;    // long-line solve: lines per workgroup
+  const uint16_t* map_line = nullptr;
+  unsigned grid_line = 0;
+  size_t smem_line = 0;
   int64_t nodes = 0;  // grid nodes over all instances
   int plane_steps = 0;  // plane solve of the last two axes (0: passes)
   const uint16_t* map_plane = nullptr;
@@ -914,16 +981,29 @@ int launch_tri_cw(const Exec& E, hipStream_t st) {
   return DOT_OK;
 }
 
+template <typename T, int D>
+int launch_tri_line(const Exec& E, hipStream_t st) {
+  auto fn = kb_tri_line<T, D>;
+  static const int smem_rc = set_max_lds((const void*)fn, E.device);
+  if (smem_rc) return smem_rc;
+  ProfScope ps(E.prof, DOT_K_DCT_LAST, st);
+  hipLaunchKernelGGL(fn, dim3(E.grid_line), dim3(kTriThreads), E.smem_line, st, (const Inst<T>*)E.d_inst, E.map_line,
+                     E.cw_line);
+  HIP_OK(hipGetLastError());
+  return DOT_OK;
+}
+
 // Last-axis elimination: the partitioned solve for lines of up to
-// kTriPartMaxNodes nodes, the one-lane-per-line solve for longer ones.
+// kTriPartMaxNodes nodes, one lane per line for longer ones.
 template <typename T, int D>
 int launch_tri(const Exec& E, hipStream_t st) {
-  if (E.ntri > E.ntri_long) {
+  if (E.ntri > E.ntri_long + E.ntri_line) {
     ProfScope ps(E.prof, DOT_K_DCT_LAST, st);
     hipLaunchKernelGGL((kb_tri_part<T, D>), dim3(E.grid_axis[D]), dim3(kTriThreads), 0, st, (const Inst<T>*)E.d_inst,
                        E.map_axis[D], E.cw_axis[D]);
     HIP_OK(hipGetLastError());
   }
+  if (E.ntri_line) return launch_tri_line<T, D>(E, st);  // every long one takes it
   if (E.ntri_long == 0) return DOT_OK;
   switch (E.cw_axis[D]) {
     case kCW: return launch_tri_cw<T, D, kCW>(E, st);
@@ -1463,6 +1543,15 @@ void set_plane(Exec& E, const PlaneGeom& pg, const uint16_t* map) {
   E.smem_plane = pg.smem;
 }
 
+void set_line(Exec& E, const LineGeom& lg, const uint16_t* map) {
+  E.cw_line = lg.cw;
+  E.map_line = map;
+  E.grid_line = (unsigned)lg.blocks;
+  E.smem_line = lg.smem;
+  E.ntri_line = lg.insts;
+  if (lg.insts) E.ntri_long = 0;
+}
+
 // Single-instance executor of a plan; descriptor slot 0 (run) or 1 (steps).
 Exec plan_exec(dot_plan* P, int slot) {
   Exec E;
@@ -1475,7 +1564,7 @@ Exec plan_exec(dot_plan* P, int slot) {
   E.map_nodes = nullptr;  // one instance: blocks need no map
   E.grid_nodes = (unsigned)P->nblocks;
   E.ntri = P->tri ? 1 : 0;
-  E.ntri_long = P->tri && P->g.N[P->D] > kTriPartMaxNodes ? 1 : 0;
+  E.ntri_long = line_long(P) ? 1 : 0;
   E.nstaged = P->nblocks >= kFinStageMinRows ? 1 : 0;
   E.nodes = P->g.nb;
   for (int a = 0; a <= P->D; ++a) {
@@ -1488,6 +1577,7 @@ Exec plan_exec(dot_plan* P, int slot) {
     E.waves_axis[a] = ag.waves;
   }
   set_plane(E, plane_geom(&P, 1, P->sched), nullptr);
+  set_line(E, line_geom(&P, 1, P->sched), nullptr);
   E.fused = slot == 0 && P->fuse_ws && P->fg.nblk;
   E.grid_fuse = P->fg.nblk;
   E.lanes_fuse = fuse_waves(P->fg) * 64;
@@ -1846,6 +1936,11 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
   const PlaneGeom pg = plane_geom(plans.data(), n, s);
   if (pg.steps)
     for (int k = 0; k < n; ++k) maps.insert(maps.end(), (size_t)plane_count(plans[k]), (uint16_t)idx[k]);
+  const size_t line_off = maps.size();
+  const LineGeom lg = line_geom(plans.data(), n, s);
+  for (int k = 0; k < n && lg.insts; ++k)
+    if (line_long(plans[k]))
+      maps.insert(maps.end(), (size_t)tiles_for(plans[k]->lines[B->D], lg.cw), (uint16_t)idx[k]);
   const size_t fuse_off = maps.size();
   int64_t all_nodes = 0;
   for (dot_plan* P : plans) all_nodes += P->g.nb;
@@ -1883,11 +1978,12 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
   E.nodes = 0;
   for (dot_plan* P : plans) {
     E.ntri += P->tri ? 1 : 0;
-    E.ntri_long += P->tri && P->g.N[P->D] > kTriPartMaxNodes ? 1 : 0;
+    E.ntri_long += line_long(P) ? 1 : 0;
     E.nstaged += P->nblocks >= kFinStageMinRows ? 1 : 0;
     E.nodes += P->g.nb;
   }
   set_plane(E, pg, B->d_maps + plane_off);
+  set_line(E, lg, B->d_maps + line_off);
   B->fg = std::move(fg);
   E.map_fuse = B->d_maps + fuse_off;
   E.grid_fuse = (unsigned)fuse_blocks;
@@ -1930,7 +2026,7 @@ int batch_descriptors(dot_batch* B, void* ws, hipStream_t st) {
   std::vector<Inst<T>> host(count);
   B->E.fused = B->fuse_ws && B->E.grid_fuse;
   size_t fuse_off = 0;
-  uint32_t blk = 0, fblk = 0, plane = 0;
+  uint32_t blk = 0, fblk = 0, plane = 0, line = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
   for (int i = 0; i < count; ++i) {
     dot_plan* P = B->plans[i];
@@ -1942,6 +2038,8 @@ int batch_descriptors(dot_batch* B, void* ws, hipStream_t st) {
     fblk += B->fg[i].nblk;
     host[i].plane0 = plane;
     plane += (uint32_t)plane_count(P);
+    host[i].line0 = line;
+    if (B->E.ntri_line && line_long(P)) line += (uint32_t)tiles_for(P->lines[B->D], B->E.cw_line);
     for (int a = 0; a <= B->D; ++a) {
       host[i].tile0[a] = tile[a];
       tile[a] += (uint32_t)tiles_for(P->lines[a], B->E.cw_axis[a]);
@@ -2144,8 +2242,9 @@ int tune_schedule(Apply&& apply, const std::vector<std::vector<std::pair<int, in
     rule_x.cw[a] = E.cw_axis[a];
     rule_x.waves[a] = E.waves_axis[a];
   }
-  const Sched first = E.plane_steps ? rule : rule_x;  // what runs without a schedule
-  if (E.plane_steps && ((rc = apply(rule_x, &E)) || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t_best))))
+  const bool own = E.plane_steps || E.ntri_line;  // launches that no schedule names
+  const Sched first = own ? rule : rule_x;        // what runs without a schedule
+  if (own && ((rc = apply(rule_x, &E)) || (rc = time_passes<T, D>(E, st, ev.e[0], ev.e[1], &t_best))))
     return rc;
   Sched best = rule_x;
   int n = 1;
@@ -2266,6 +2365,7 @@ void dot_plan_destroy(dot_plan* P) {
   (void)hipFree(P->step_ctl);
   (void)hipFree(P->step_partials);
   (void)hipFree(P->step_cbuf);
+  (void)hipFree(P->piv);
   (void)hipFree(P->step_scratch);
   (void)hipFree(P->fuse_ws);
   (void)hipHostFree(P->host_ctl);
@@ -2358,6 +2458,10 @@ int dot_plan_create(const dot_problem* p, dot_plan** out) {
   }
   rc = P->precision == DOT_FP64 ? build_eigs<double>(P.get()) : build_eigs<float>(P.get());
   if (rc) return rc;
+  if (line_long(P.get()) && line_pays(P->lines[D], g.N[D])) {
+    rc = P->precision == DOT_FP64 ? build_pivots<double>(P.get()) : build_pivots<float>(P.get());
+    if (rc) return rc;
+  }
   const size_t pb = (size_t)g.nb * P->scalar_bytes;
   const StateLayout lay = state_layout(D, g.nb, P->precision);
   P->off_phi = lay.off_phi;
@@ -3373,7 +3477,8 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   }
   // descriptors of the active instances, in slot order
   const PlaneGeom pg = plane_geom(act.data(), (int)act.size(), Sched());
-  uint32_t blk = 0, plane = 0;
+  const LineGeom lg = line_geom(act.data(), (int)act.size(), Sched());
+  uint32_t blk = 0, plane = 0, line = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
   int idx = 0;
   for (int sl = 0; sl < C->max_slots; ++sl) {
@@ -3386,6 +3491,8 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
     blk += (uint32_t)P->nblocks;
     s.plane0 = plane;
     plane += (uint32_t)plane_count(P);
+    s.line0 = line;
+    if (lg.insts && line_long(P)) line += (uint32_t)tiles_for(P->lines[C->D], lg.cw);
     for (int a = 0; a <= C->D; ++a) {
       s.tile0[a] = tile[a];
       tile[a] += (uint32_t)tiles_for(P->lines[a], E.cw_axis[a]);
@@ -3399,7 +3506,7 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   E.grid_nodes = blk;
   for (dot_plan* P : act) {
     E.ntri += P->tri ? 1 : 0;
-    E.ntri_long += P->tri && P->g.N[P->D] > kTriPartMaxNodes ? 1 : 0;
+    E.ntri_long += line_long(P) ? 1 : 0;
     E.nstaged += P->nblocks >= kFinStageMinRows ? 1 : 0;
     E.nodes += P->g.nb;
   }
@@ -3428,6 +3535,10 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   const size_t plane_off = maps.size();
   if (pg.steps)
     for (size_t k = 0; k < act.size(); ++k) maps.insert(maps.end(), (size_t)plane_count(act[k]), (uint16_t)k);
+  const size_t line_off = maps.size();
+  for (size_t k = 0; k < act.size() && lg.insts; ++k)
+    if (line_long(act[k]))
+      maps.insert(maps.end(), (size_t)tiles_for(act[k]->lines[C->D], lg.cw), (uint16_t)k);
   if (host.size() * sizeof(Inst<T>) > C->d_inst_cap) {
     (void)hipFree(C->d_inst);
     C->d_inst_cap = host.size() * sizeof(Inst<T>) * 2;
@@ -3444,6 +3555,7 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   E.d_inst = C->d_inst;
   E.map_nodes = C->d_maps;
   set_plane(E, pg, C->d_maps + plane_off);
+  set_line(E, lg, C->d_maps + line_off);
   for (int a = 0; a <= C->D; ++a) E.map_axis[a] = C->d_maps + map_off[a];
   C->dirty = false;
   return DOT_OK;

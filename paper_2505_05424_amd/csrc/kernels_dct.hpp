@@ -615,6 +615,141 @@ __device__ __forceinline__ void tri_pass_body(const Geo& g, T* __restrict__ plan
   }
 }
 
+// ---- one-lane elimination of few long lines ------------------------------------
+// The systems, steps and rounding of tri_pass_body for launches of few lines,
+// whose time is the chain along one line: one lane of one wave, which issues
+// an instruction every few cycles. There the pivots (a reciprocal and its
+// refinement per node, twice) and the chunks' trips through memory were most
+// of a node's 200 ns. Here nothing is left in the chain but its own steps: the
+// pivots, which depend on the grid alone, come from a table that the plan
+// holds (tri_pivots), the tile's lines and pivots are in LDS whole, as FP64,
+// and the conversions and c' are done by all threads between the two sweeps.
+constexpr int kTriLineMax = 16;                    // lines of a workgroup, at most
+constexpr size_t kTriLineLds = (size_t)150 << 10;  // LDS of a workgroup, at most
+// LDS row of a line: odd, so that the lanes of different lines differ in bank.
+__host__ __device__ constexpr int tri_line_stride(int L) { return L | 1; }
+constexpr size_t tri_line_bytes(int L) { return (size_t)tri_line_stride(L) * 2 * sizeof(double); }
+
+// Pivot reciprocals of line `line`, at node i of the plane.
+template <typename T>
+__device__ __forceinline__ void tri_pivots(const Geo& g, const T* __restrict__ lam_other, double* __restrict__ piv,
+                                           int64_t line) {
+  const int L = g.N[g.D];
+  const double s2 = (double)g.n[g.D] * (double)g.n[g.D];
+  const double lam = (double)glob(lam_other)[line];
+  gp<double> out = glob(piv) + (size_t)line * (size_t)L;
+  double cp = 0.0, r = 0.0;
+  for (int i = 0; i < L; ++i) {
+    if (lam != 0.0) cp = tri_cstep(lam, s2, i, L, cp, &r);
+    out[i] = r;
+  }
+}
+
+// Runs step(b_i, r_i) over the nodes of a line in order (of decreasing i
+// with REV) and keeps what it returns in place of b_i; blocks of 8 nodes, the
+// next one read from LDS while one is computed.
+template <bool REV, typename Step>
+__device__ __forceinline__ void tri_chain(double* b, const double* r, int L, Step&& step) {
+  constexpr int U = 8;
+  auto at = [&](int i) { return REV ? L - 1 - i : i; };
+  auto read = [&](int i, double (&bo)[U], double (&ro)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      bo[u] = b[at(i + u)];
+      ro[u] = r[at(i + u)];
+    }
+  };
+  auto block = [&](int i, const double (&bv)[U], const double (&rv)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) b[at(i + u)] = step(bv[u], rv[u]);
+  };
+  const int n2 = L / (2 * U) * (2 * U);
+  if (n2 > 0) {
+    double b0[U], r0[U], b1[U], r1[U];
+    read(0, b0, r0);
+    for (int i = 0; i < n2; i += 2 * U) {
+      read(i + U, b1, r1);
+      block(i, b0, r0);
+      read(min(i + 2 * U, n2 - U), b0, r0);  // past the last block: not used
+      block(i + U, b1, r1);
+    }
+  }
+  for (int i = n2; i < L; ++i) b[at(i)] = step(b[at(i)], r[at(i)]);
+}
+
+template <typename T>
+__device__ __forceinline__ void tri_line_body(const Geo& g, T* __restrict__ plane, const double* __restrict__ piv,
+                                              const T* __restrict__ lam_other, int64_t blk, int cw) {
+  extern __shared__ unsigned char smem_raw[];
+  const int L = g.N[g.D], S = tri_line_stride(L);
+  const double s2 = (double)g.n[g.D] * (double)g.n[g.D];
+  const double inv_s2 = 1.0 / s2;
+  const int64_t ncols = g.nb / L, c0 = blk * cw;
+  const int nl = (int)((ncols - c0) < cw ? (ncols - c0) : cw);
+  double* mean = reinterpret_cast<double*>(smem_raw);  // of each line (zero but on the singular one)
+  double* rt = mean + kTriLineMax;
+  double* bt = rt + (size_t)cw * S;
+  gp<T> pl = glob(plane) + (size_t)c0 * (size_t)L;
+  gp<const double> pv = glob(piv) + (size_t)c0 * (size_t)L;
+  constexpr int kPer = 8;  // elements in flight per thread
+  for (int l = 0; l < nl; ++l) {
+    for (int i0 = threadIdx.x; i0 < L; i0 += kPer * kTriThreads) {
+      T b[kPer];
+      double r[kPer];
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int i = min(i0 + u * kTriThreads, L - 1);
+        b[u] = pl[(size_t)l * L + i];
+        r[u] = pv[(size_t)l * L + i];
+      }
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const int i = i0 + u * kTriThreads;
+        if (i < L) {
+          bt[l * S + i] = (double)b[u];
+          rt[l * S + i] = r[u];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  // lane l of the first wave runs line l; the line with lam = 0, if it is
+  // here, runs in the second wave beside them
+  const int me = threadIdx.x & 63;
+  const bool zero = me < nl && threadIdx.x < 128 && glob(lam_other)[c0 + me] == T(0);
+  const bool owner = me < nl && threadIdx.x < 128 && (threadIdx.x >= 64) == zero;
+  double* b = bt + (owner ? me : 0) * S;
+  double* r = rt + (owner ? me : 0) * S;
+  if (owner && zero) {
+    double cp = 0.0, dp = 0.0, sum = 0.0;
+    tri_chain<false>(b, r, L, [&](double bj, double) {
+      const double d = dp;
+      sum += d;
+      cp -= bj;
+      dp += cp * inv_s2;
+      return d;
+    });
+    mean[me] = sum / (double)L;
+  } else if (owner) {
+    double dp = 0.0;
+    tri_chain<false>(b, r, L, [&](double bj, double rj) { return dp = (bj + s2 * dp) * rj; });
+    mean[me] = 0.0;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < cw * S; e += kTriThreads) {
+    bt[e] = (double)(T)bt[e];
+    rt[e] = (double)(T)(-s2 * rt[e]);
+  }
+  __syncthreads();
+  if (owner && !zero) {
+    double x = 0.0;
+    tri_chain<true>(b, r, L, [&](double d, double c) { return x = d - c * x; });
+  }
+  __syncthreads();
+  for (int l = 0; l < nl; ++l)
+    for (int i = threadIdx.x; i < L; i += kTriThreads) pl[(size_t)l * L + i] = (T)(bt[l * S + i] - mean[l]);
+}
+
 // ---- partitioned elimination of the last-axis line systems -------------------
 // The same line systems as tri_pass_body, (lam + n^2 L_path) x = b along each
 // line of the last axis, solved with P lanes per line instead of one. Lane k
