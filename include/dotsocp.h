@@ -313,8 +313,8 @@ int dot_test_fail_captures(int32_t count);
  * solve takes (8 for lines of up to 288 nodes, 4 up to 576; 64 when some
  * line is longer); waves do not apply.
  * Without a schedule, launches of few small planes solve the last two axes in
- * one workgroup per plane instead (axes of up to 72 points, 512 planes), with
- * the same bits; a schedule that was set always runs the passes, and so does
+ * one workgroup per plane instead (axes of up to 72 points; up to 512 planes,
+ * 1024 in mixed precision), with the same bits; a schedule that was set always runs the passes, and so does
  * one that an autotune call found faster. */
 typedef struct {
   int32_t cw[4];       /* lines per tile, axes 0..D: 16, 32 or 64, also 4 or 8 on an eliminated last

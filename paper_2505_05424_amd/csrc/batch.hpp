@@ -15,8 +15,10 @@
 
 namespace dot {
 
+// Every workgroup starts by reading its descriptor: what the sweeps and the
+// passes read stands together, in whole 64-byte lines.
 template <typename T>
-struct Inst {
+struct alignas(64) Inst {
   Geo g;
   double* phi;      // FP64 potential
   T* work;          // transform work plane: phi itself (FP64) or the FP32 scratch
@@ -33,11 +35,11 @@ struct Inst {
   const double* c_hi;
   const T* lam_other;
   const T* lam_last;
-  AxisTab<T> tab[kMaxAxes];
-  FinArgs fa;
   uint32_t blk0;             // first block in the per-node grid
   uint32_t tile0[kMaxAxes];  // first tile in each axis-pass grid
   int32_t tri;               // last axis solved by tridiagonal elimination (else transform, 1/Lambda, transform)
+  AxisTab<T> tab[kMaxAxes];
+  FinArgs fa;
   // one-sweep iteration: the second place of beta and alpha (the first is beta
   // and alpha above), the plane of its right-hand side and, at checks, of each
   // cell's |z - B F q_new - d|^2, and its workgroups

@@ -191,7 +191,7 @@ struct dot_plan {
   int64_t partial_rows = 0;  // capacity of the partial-sum rows (nsweep at one slice per workgroup)
   int64_t lines[kMaxAxes] = {0, 0, 0, 0};  // lines per axis (nb / N[a])
   bool wide_ok[kMaxAxes] = {true, true, true, true};  // the axis fits a tile of kCW lines
-  bool mid_ok[kMaxAxes] = {true, true, true, true};   // a tile of kCWMid lines fits in kMidLds
+  bool mid_ok[kMaxAxes] = {true, true, true, true};   // the axis fits a tile of kCWMid lines
   bool tri = false;      // the last axis is solved by tridiagonal elimination
   double* piv = nullptr;    // pivots of the last axis's lines, where line_pays
   void* step_cbuf = nullptr;  // c' plane of the tridiagonal solve for step-level calls
@@ -323,13 +323,10 @@ int build_axis(dot_plan* P, int a, void** buf, AxisTab<T>* tab) {
   all.insert(all.end(), fo.begin(), fo.end());
   all.insert(all.end(), ie.begin(), ie.end());
   all.insert(all.end(), io.begin(), io.end());
-  size_t lane_at[4] = {0, 0, 0, 0};
-  const bool lanes = L <= kPlaneAxis;
-  if (lanes) {
+  if (L <= kPlaneAxis) {  // lane-major (plane_tab)
     const std::vector<T>* frag[4] = {&fe, &fo, &ie, &io};
     for (int i = 0; i < 4; ++i) {
       const int n = i % 2 ? no : ne, rb = (n + 15) / 16, kr = (n + 3) / 4, nch = ksteps(n) / kU + 1;
-      lane_at[i] = all.size();
       for (int m = 0; m < rb; ++m)
         for (int s = 0; s < kr; ++s)
           for (int l = 0; l < 64; ++l) all.push_back((*frag[i])[(((size_t)m * nch + s / kU) * 64 + l) * kU + s % kU]);
@@ -343,7 +340,6 @@ int build_axis(dot_plan* P, int a, void** buf, AxisTab<T>* tab) {
   tab->fo = d + fe.size();
   tab->ie = d + fe.size() + fo.size();
   tab->io = d + fe.size() + fo.size() + ie.size();
-  for (int i = 0; i < 4; ++i) tab->pl[i] = lanes ? d + lane_at[i] : nullptr;
   tab->L = L;
   tab->M = M;
   tab->ne = ne;
@@ -355,13 +351,6 @@ int build_axis(dot_plan* P, int a, void** buf, AxisTab<T>* tab) {
   return DOT_OK;
 }
 
-// Waves per workgroup of a transform pass over an axis of L points. A launch
-// with few tiles (fewer than kManyTiles workgroups) gives each work item its
-// own wave, so the coefficient streams of all items run concurrently; with
-// many tiles each wave takes up to items_per_wave items and more workgroups
-// share a CU.
-constexpr int64_t kManyTiles = 1024;
-
 int pass_items(int L, int cw) {
   const int M = L / 2, ne = L - M, no = M;
   const int groups = cw >= 32 ? cw / 32 : 1;  // work items per row block (see tile_mfma)
@@ -371,15 +360,6 @@ int pass_items(int L, int cw) {
 template <typename T>
 int wave_items(int cw) {
   return cw >= 32 ? items_per_wave<T, kCW>() : items_per_wave<T, kCWNarrow>();
-}
-
-template <typename T>
-int pass_waves(int L, int64_t tiles, int cw) {
-  const int items = pass_items(L, cw);
-  const int rounds = (items + wave_items<T>(cw) - 1) / wave_items<T>(cw);
-  // many tiles: small workgroups, several per CU; few tiles: spread the items
-  const int w = (tiles >= kManyTiles || items > kMaxWaves) ? rounds : items;
-  return std::max(4, std::min(kMaxWaves, w));
 }
 
 // Dynamic LDS of a transform pass over an axis of L points: the tile of
@@ -395,18 +375,65 @@ bool axis_fits(int L, int cw, int max_smem) {
          (int64_t)pass_smem(L, sizeof(T), cw) <= (int64_t)max_smem;
 }
 
+// Workgroups of a transform launch that share a CU: as many as there are, and
+// as its LDS holds.
+constexpr int64_t kPassCUs = 256;
+constexpr size_t kPassLds = 160 << 10;
+int64_t pass_per_cu(int64_t tiles, size_t smem) {
+  return std::min((tiles + kPassCUs - 1) / kPassCUs, std::max<int64_t>(1, (int64_t)(kPassLds / smem)));
+}
+
+// Waves per workgroup of a transform pass. A CU holds 16 waves of the FP64
+// kernels (124 registers) and 20 of the FP32 ones (86), so the workgroups that
+// should share a CU get an equal part of those: one takes a wave per work item
+// and a few more for the loads, two take eight, up to four take four. With
+// more, smaller ones hide each other's loads best (half as many waves as
+// items), but for the last axis, which runs two transforms on a tile. Measured
+// (us per iteration, waves): 2D 64x128^2 FP64 axis 1, 263 tiles of 32, 9 waves
+// 184.2, 8 waves 176.4 (nine fit a CU once, and seven tiles wait for a second
+// round); 48x150x131 FP64 axis 1, 405 tiles of 16, 10 waves 146.3, 8 waves
+// 140.7; 30x420x60 FP64 axis 1, 119 tiles, 5 waves 150.6, 16 waves 129.5; 3D
+// 32x64^3 FP64 time axis, 4292 tiles of 64, 4 waves 1825.0, 3 waves 1803.5;
+// 16x48x50x60 FP64 axis 1, 1653 tiles of 32, 4 waves 510.6, 2 waves 505.2.
+template <typename T>
+int pass_waves(int L, int64_t tiles, int cw, size_t smem, bool last) {
+  const bool f32 = sizeof(T) == 4;
+  const int items = pass_items(L, cw);
+  const int rounds = (items + wave_items<T>(cw) - 1) / wave_items<T>(cw);
+  const int64_t n = pass_per_cu(tiles, smem);
+  int w;
+  if (n <= 1)
+    w = std::min(std::max(items, cw == kCWNarrow ? 8 : 12), 2 * items);
+  else if (n == 2)
+    w = items > 4 ? 8 : 4;
+  else if (n <= 4)
+    w = f32 && items == 5 ? 5 : 4;
+  else if (last || (f32 && n == 5))
+    w = 4;
+  else
+    w = std::min(4, std::max(2, (items + 1) / 2));
+  return std::max(rounds, std::min(kMaxWaves, w));
+}
+
 // Tile width of a transform launch over `lines` lines in all: the wide tile
-// when every axis of the launch fits it and it still gives many workgroups;
-// else the middle width when its tile is small enough for several workgroups
-// per CU (kMidLds) and the launch keeps kMidTiles tiles (half the
-// coefficient traffic of the narrow tile; measured: 2D 64x128^2 mixed 167 ->
-// 153 us per iteration, neutral where the LDS or the tile count rule it out);
-// else the narrow one.
-constexpr int64_t kMidTiles = 256;
+// when every axis of the launch fits it and it still gives four workgroups
+// per CU; else the middle width, which reads the coefficients half as often as
+// the narrow one, where its tiles keep most CUs busy and the LDS holds the
+// tiles that share a CU (or four); else the narrow one. Measured (us per
+// iteration, 16 against 32 lines): 48x150x131 FP64 axis 1, 203 tiles of 32,
+// 139.9 / 137.1 and mixed 106.0 / 101.6; 32x200x180 FP64 axis 1, 187 tiles,
+// 191.9 / 185.5; 40x120x70 FP64 last axis, 156 tiles, 71.4 / 70.1, but axis 1,
+// 91 tiles, 71.6 / 73.4; 64x256^2 FP64 axis 1, 523 tiles of which two fit a
+// CU, 510.8 / 512.5.
+constexpr int64_t kWideTiles = 4 * kPassCUs;
+constexpr int64_t kMidTiles = 150;
 constexpr size_t kMidLds = 40 << 10;
-int choose_cw(int64_t lines, bool wide_ok, bool mid_ok) {
-  if (wide_ok && (lines + kCW - 1) / kCW >= kManyTiles) return kCW;
-  if (mid_ok && (lines + kCWMid - 1) / kCWMid >= kMidTiles) return kCWMid;
+int choose_cw(int64_t lines, bool wide_ok, bool mid_ok, size_t mid_smem) {
+  if (wide_ok && (lines + kCW - 1) / kCW >= kWideTiles) return kCW;
+  const int64_t mid = (lines + kCWMid - 1) / kCWMid;
+  if (mid_ok && mid >= kMidTiles &&
+      (mid_smem <= kMidLds || (mid + kPassCUs - 1) / kPassCUs <= (int64_t)(kPassLds / mid_smem)))
+    return kCWMid;
   return kCWNarrow;
 }
 
@@ -446,6 +473,14 @@ template <typename T>
 AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
   int64_t all_lines = 0;
   bool wide_ok = true, mid_ok = true, all_tri = true;
+  const bool last = a == plans[0]->D;
+  auto transformed = [&](const dot_plan* P) { return !(last && P->tri); };  // else eliminated
+  auto smem = [&](int cw) {
+    size_t m = 0;
+    for (int i = 0; i < count; ++i)
+      if (transformed(plans[i])) m = std::max(m, pass_smem(plans[i]->g.N[a], (int)sizeof(T), cw));
+    return m;
+  };
   for (int i = 0; i < count; ++i) {
     all_lines += plans[i]->lines[a];
     wide_ok = wide_ok && plans[i]->wide_ok[a];
@@ -454,14 +489,14 @@ AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
   }
   AxisGeom ag;
   ag.cw = s.cw[a] ? s.cw[a]
-                  : ((a == plans[0]->D && all_tri) ? tri_default_cw(plans, count) : choose_cw(all_lines, wide_ok, mid_ok));
+                  : ((last && all_tri) ? tri_default_cw(plans, count)
+                                       : choose_cw(all_lines, wide_ok, mid_ok, smem(kCWMid)));
   for (int i = 0; i < count; ++i) ag.tiles += tiles_for(plans[i]->lines[a], ag.cw);
+  ag.smem = smem(ag.cw);
   int waves = 1;
-  for (int i = 0; i < count; ++i) {
-    if (a == plans[i]->D && plans[i]->tri) continue;  // takes the tridiagonal solve on this axis
-    ag.smem = std::max(ag.smem, pass_smem(plans[i]->g.N[a], (int)sizeof(T), ag.cw));
-    waves = std::max(waves, pass_waves<T>(plans[i]->g.N[a], ag.tiles, ag.cw));
-  }
+  for (int i = 0; i < count; ++i)
+    if (transformed(plans[i]))
+      waves = std::max(waves, pass_waves<T>(plans[i]->g.N[a], ag.tiles, ag.cw, ag.smem, last));
   ag.waves = s.waves[a] ? s.waves[a] : waves;
   return ag;
 }
@@ -472,14 +507,17 @@ AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
 // eliminated, a schedule that was set (it names passes), or no gain. The rule
 // (us per iteration, passes -> plane solve): the launches that it saves are
 // all there is to gain, so it holds while the planes are solved in at most two
-// rounds over the CUs (FP64 400x20^2 107.3 -> 102.0, 20^4 71.5 -> 66.8, 1D
-// 16x32 23.7 -> 17.3; 12x40x27x31, 533 planes, 116.1 -> 116.8, 900x15^2 217.9
-// -> 221.8; mixed 85.0 -> 77.0, 62.5 -> 55.3, 23.8 -> 16.9, 90.8 -> 87.0, 184.7
-// -> 182.6) and, in FP64, up to 4096 points, past which a wave takes a second
-// line block (32x63^2 47.7 -> 45.5, 64x32x64 51.4 -> 47.8, but 32x64^2 51.4 ->
-// 54.6; mixed 43.7 -> 38.2, 44.9 -> 38.8, 46.2 -> 43.4).
+// rounds over the CUs, of which each holds one FP64 plane or two FP32 ones
+// (FP64 400x20^2 84.8 -> 80.5, 20^4 71.4 -> 67.2, 1D 16x32 23.7 -> 17.3;
+// 12x40x27x31, 533 planes, 112.8 -> 112.7, 900x15^2 217.9 -> 221.8; mixed 67.4
+// -> 61.3, 62.8 -> 56.3, 23.8 -> 16.9, 90.8 -> 88.2; more than 512 only of 640
+// points: 900x64^2 506.6 -> 491.2, but 20x40x10^2, 861 planes, 52.2 -> 53.7)
+// and, in FP64, up to 4096 points, past which a wave takes a second line block
+// (32x63^2 47.7 -> 45.5, 64x32x64 51.4 -> 47.8, but 32x64^2 51.4 -> 54.6; mixed
+// 43.7 -> 38.2, 44.9 -> 38.8, 46.2 -> 43.4).
 constexpr int64_t kPlaneCount = 512;
 constexpr int kPlanePoints64 = 4096;
+constexpr int kPlanePointsTwo = 640;
 struct PlaneGeom {
   int steps = 0;
   int64_t blocks = 0;
@@ -489,18 +527,20 @@ int64_t plane_count(const dot_plan* P) { return P->g.nb / ((int64_t)P->g.N[P->D 
 PlaneGeom plane_geom(dot_plan* const* plans, int count, const Sched& s) {
   PlaneGeom pg;
   if (!s.rule()) return pg;
-  int longest = 0;
+  int longest = 0, least = kPlaneAxis * kPlaneAxis;
   for (int i = 0; i < count; ++i) {
     const dot_plan* P = plans[i];
     const int N1 = P->g.N[P->D - 1], N2 = P->g.N[P->D];
     if (P->tri || std::max(N1, N2) > kPlaneAxis) return PlaneGeom();
     if (P->precision == DOT_FP64 && N1 * N2 > kPlanePoints64) return PlaneGeom();
     longest = std::max({longest, N1, N2});
+    least = std::min(least, N1 * N2);
     const int row = P->precision == DOT_FP64 ? plane_stride<double>(N2) : plane_stride<float>(N2);
     pg.smem = std::max(pg.smem, ((size_t)N1 * row + N1 + N2) * P->scalar_bytes);
     pg.blocks += plane_count(P);
   }
-  if (pg.blocks > kPlaneCount) return PlaneGeom();
+  const bool twice = plans[0]->precision != DOT_FP64 && least >= kPlanePointsTwo;
+  if (pg.blocks > (twice ? 2 : 1) * kPlaneCount) return PlaneGeom();
   pg.steps = longest > 64 ? 9 : 8;
   for (int i = 0; i < count; ++i) {
     const int N1 = plans[i]->g.N[plans[i]->D - 1], N2 = plans[i]->g.N[plans[i]->D];
@@ -2429,7 +2469,7 @@ int dot_plan_create(const dot_problem* p, dot_plan** out) {
     if (!fits(kCWNarrow))
       return fail(DOT_EINVAL, "axis of " + std::to_string(g.N[a]) + " nodes exceeds the transform tile capacity");
     P->wide_ok[a] = fits(kCW);
-    P->mid_ok[a] = fits(kCWMid) && pass_smem(g.N[a], P->scalar_bytes, kCWMid) <= kMidLds;
+    P->mid_ok[a] = fits(kCWMid);
   }
   // problem data
   const int64_t nx = g.nx;
@@ -3462,18 +3502,13 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
     C->dirty = false;
     return DOT_OK;
   }
-  // transform tile width per axis, from the lines of all active instances
+  AxisGeom ag[kMaxAxes];
   for (int a = 0; a <= C->D; ++a) {
-    int64_t all_lines = 0;
-    bool wide_ok = true, mid_ok = true, all_tri = true;
-    for (dot_plan* P : act) {
-      all_lines += P->lines[a];
-      wide_ok = wide_ok && P->wide_ok[a];
-      mid_ok = mid_ok && P->mid_ok[a];
-      all_tri = all_tri && P->tri;
-    }
-    E.cw_axis[a] = (a == C->D && all_tri) ? tri_default_cw(act.data(), (int)act.size())
-                                           : choose_cw(all_lines, wide_ok, mid_ok);
+    ag[a] = axis_geom<T>(act.data(), (int)act.size(), a, Sched());
+    E.cw_axis[a] = ag[a].cw;
+    E.grid_axis[a] = (unsigned)ag[a].tiles;
+    E.smem_axis[a] = ag[a].smem;
+    E.waves_axis[a] = ag[a].waves;
   }
   // descriptors of the active instances, in slot order
   const PlaneGeom pg = plane_geom(act.data(), (int)act.size(), Sched());
@@ -3513,24 +3548,8 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   size_t map_off[kMaxAxes] = {0, 0, 0, 0};
   for (int a = 0; a <= C->D; ++a) {
     map_off[a] = maps.size();
-    size_t smem = 0;
-    int waves = 1, k = 0;
-    const int cw = E.cw_axis[a];
-    int64_t all_tiles = 0;
-    for (dot_plan* P : act) all_tiles += tiles_for(P->lines[a], cw);
-    for (int sl = 0; sl < C->max_slots; ++sl) {
-      Request* r = C->slots[sl];
-      if (!r) continue;
-      dot_plan* P = r->plan;
-      maps.insert(maps.end(), (size_t)tiles_for(P->lines[a], cw), (uint16_t)k);
-      ++k;
-      if (a == C->D && P->tri) continue;  // takes the tridiagonal solve on this axis
-      smem = std::max(smem, pass_smem(P->g.N[a], P->scalar_bytes, cw));
-      waves = std::max(waves, pass_waves<T>(P->g.N[a], all_tiles, cw));
-    }
-    E.grid_axis[a] = (unsigned)(maps.size() - map_off[a]);
-    E.smem_axis[a] = smem;
-    E.waves_axis[a] = waves;
+    for (size_t k = 0; k < act.size(); ++k)
+      maps.insert(maps.end(), (size_t)tiles_for(act[k]->lines[a], ag[a].cw), (uint16_t)k);
   }
   const size_t plane_off = maps.size();
   if (pg.steps)

@@ -55,19 +55,16 @@ template <> struct MfmaOps<float> {
 // and holds H[16 m + lane % 16][4 s + lane / 16] (zero outside H), so one
 // lane reads its kU fragments of a chunk as one contiguous vector; the extra
 // zero chunk per row block lets the prefetch run past the end unguarded. With C[k][j] = s_k cos(pi k (2j+1) / (2L)) the halves are
-// The lane-major copy pl has element (m, s, lane) at (m * steps + s) * 64 + lane,
-// steps = the k-steps that hold inputs: one coalesced load per k-step.
 //   forward even  H[k'][j] = C[2k'][j]    (j < ne: u_0..u_{M-1}, middle point)
 //   forward odd   H[k'][j] = C[2k'+1][j]  (j < no: v_j)
 //   inverse even  H[j][k'] = C[2k'][j]    (outputs E_j from X_{2k'})
 //   inverse odd   H[j][k'] = C[2k'+1][j]  (outputs O_j from X_{2k'+1})
 template <typename T>
-struct AxisTab {
+struct alignas(64) AxisTab {
   const T* fe;
   const T* fo;
   const T* ie;
   const T* io;
-  const T* pl[4];  // fe, fo, ie, io again, lane-major (the plane solve; null on long axes)
   int L, M, ne, no;
   int rb_e, rb_o, ks_e, ks_o;
 };

@@ -34,6 +34,18 @@ __host__ __device__ constexpr int plane_stride(int n) {
   return sizeof(T) == 8 ? (n | 1) : n + (2 - n % 4 + 4) % 4;
 }
 
+// The half matrices again, lane-major, follow the chunked tables of an axis
+// that the plane solve may take (fe, fo, ie, io, then these four in the same
+// order): element (row block m, k-step s, lane) at (m * steps + s) * 64 + lane,
+// steps = the k-steps that hold inputs, so a k-step is one coalesced load.
+// Offset of the one asked for from fe.
+template <typename T>
+__host__ __device__ inline uint32_t plane_tab(const AxisTab<T>& a, bool inv, bool odd) {
+  const uint32_t ce = (uint32_t)a.rb_e * (a.ks_e / kU + 1) * 64 * kU, co = (uint32_t)a.rb_o * (a.ks_o / kU + 1) * 64 * kU;
+  const uint32_t le = (uint32_t)a.rb_e * ((a.ne + 3) / 4) * 64, lo = (uint32_t)a.rb_o * ((a.no + 3) / 4) * 64;
+  return 2 * (ce + co) + (inv ? le + lo : 0u) + (odd ? le : 0u);
+}
+
 // Fragments of the row block of this wave (wave w of a transform: row block
 // w % R of its R, line blocks w / R, w / R + 16 / R, ...).
 template <typename T, int KS>
@@ -43,7 +55,7 @@ __device__ __forceinline__ void plane_coef(const AxisTab<T>& a, bool inv, T (&cf
   const bool odd = rb >= a.rb_e;
   const int m = odd ? rb - a.rb_e : rb;
   const int kr = ((odd ? a.no : a.ne) + 3) >> 2;
-  gp<const T> t = glob(a.pl[2 * (int)inv + (int)odd]) + (size_t)(m * kr) * 64 + (threadIdx.x & 63);
+  gp<const T> t = glob(a.fe) + plane_tab(a, inv, odd) + (uint32_t)(m * kr) * 64 + (threadIdx.x & 63);
 #pragma unroll
   for (int s = 0; s < KS; ++s) cf[s] = s < kr ? t[s * 64] : T(0);
 }

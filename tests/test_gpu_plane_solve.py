@@ -12,7 +12,7 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 GRIDS = [(1, 1), (63, 63), (71, 40), (2, 71), (64, 64), (30, 31), (5, 15, 16), (3, 63, 1), (9, 32, 64), (511, 6, 9),
-         (4, 3, 17, 47), (2, 2, 71, 62)]
+         (4, 3, 17, 47), (2, 2, 71, 62), (12, 40, 27, 31)]
 
 
 def _solve(plan, its, passes):
