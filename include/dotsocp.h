@@ -42,8 +42,9 @@
  *
  * Ownership: the caller owns every buffer it passes; the library keeps no
  * pointer to caller memory after a call returns. A dot_plan owns small
- * constant tables on its device (transform matrices, eigenvalues, weights)
- * and, from its first dot_run on a large 1D or 2D grid, a buffer of D+3 double
+ * constant tables on its device (transform matrices, eigenvalues, weights;
+ * with few last-axis lines of more than 576 nodes also the pivots of their
+ * elimination, one double plane of at most some 40 MB) and, from its first dot_run on a large 1D or 2D grid, a buffer of D+3 double
  * planes that its iterations use beside the state (about a sixth of the
  * state; a batch holds one for its members). Where the device has no memory
  * left for it, runs take the launches of smaller grids: slower, same results.
