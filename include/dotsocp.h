@@ -234,16 +234,22 @@ typedef enum {
   DOT_K_RESID = 7,     /* residual partial sums (checks only) */
   DOT_K_FINAL = 8,     /* residual finalize + sigma rule (checks only) */
   DOT_K_RHS = 9,       /* right-hand side A^*(q - alpha/sigma) - c/sigma (mixed: its defect) */
+  DOT_K_SWEEP = 10,    /* z-step, q-step, multiplier steps and next right-hand side in one sweep
+                          (large 1D and 2D runs) */
+  DOT_K_PLANE = 11,    /* both transforms of the last two axes, forward and inverse, in one launch
+                          (few small planes) */
   DOT_K_NONE = -1
 } dot_kernel_class;
 
 /* Record HIP events around every launch of one kernel class inside dot_run
  * on its stream (DOT_K_NONE switches recording off); dot_profile_read returns
  * the summed event time in ms and the number of launches since the last read
- * and clears them. While a class is recorded, graphs are off and every class
- * runs as its own launch (otherwise an iteration without a residual check
- * computes the next iteration's z-step and right-hand side inside its beta
- * launch, and large instances run the z-step beside the phi-step). */
+ * and clears them. While a class is recorded, graphs are off. While one of the
+ * first ten is, every one of those runs as its own launch: no sweep or plane
+ * launches, no next z-step and right-hand side inside the beta launch, no
+ * z-step beside the phi-step. DOT_K_SWEEP and DOT_K_PLANE record the launches
+ * of a run as it is without recording; a run that has none records none. The
+ * iterates are the same either way. */
 int dot_profile_select(dot_plan* plan, int32_t kernel_class);
 int dot_profile_read(dot_plan* plan, double* total_ms, int64_t* launches);
 

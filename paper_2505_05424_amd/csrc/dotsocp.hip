@@ -1055,6 +1055,7 @@ int launch_tri(const Exec& E, hipStream_t st) {
 template <typename T, int D, int SRC, int DST, int KS>
 int launch_plane_ks(const Exec& E, hipStream_t st) {
   auto fn = kb_plane<T, D, SRC, DST, KS>;
+  ProfScope ps(E.prof, DOT_K_PLANE, st);
   hipLaunchKernelGGL(fn, dim3(E.grid_plane), dim3(kPlaneThreads), E.smem_plane, st, (const Inst<T>*)E.d_inst,
                      E.map_plane);
   HIP_OK(hipGetLastError());
@@ -1066,6 +1067,10 @@ int launch_plane(const Exec& E, hipStream_t st) {
   return E.plane_steps == 8 ? launch_plane_ks<T, D, SRC, DST, 8>(E, st) : launch_plane_ks<T, D, SRC, DST, 9>(E, st);
 }
 
+// Whether a kernel class of the separate launches is being timed: each of those
+// then runs by itself.
+bool split_classes(const Exec& E) { return E.prof && E.prof->cls >= 0 && E.prof->cls < DOT_K_SWEEP; }
+
 // The 2D+1 transform passes of one Poisson solve (a3 + a4): first pass on the
 // time axis loads according to SRC, forward passes on the middle axes, the
 // fused forward/scale/inverse pass on the last axis (or, for instances with
@@ -1074,8 +1079,8 @@ int launch_plane(const Exec& E, hipStream_t st) {
 template <typename T, int D, int SRC, int DST>
 int run_passes(const Exec& E, int par, double sigma, hipStream_t st) {
   int rc;
-  if (E.plane_steps && !(E.prof && E.prof->cls >= 0)) {
-    // the last two axes in one launch (kernel classes timed one by one run as passes)
+  if (E.plane_steps && !split_classes(E)) {
+    // the last two axes in one launch
     if constexpr (D == 1) {
       return launch_plane<T, D, SRC, DST>(E, st);
     } else {
@@ -1228,6 +1233,7 @@ int launch_fuse(const Exec& E, int par, bool rhs, bool check, hipStream_t st) {
     constexpr bool kMixed = !std::is_same<T, double>::value;
     const Inst<T>* I = (const Inst<T>*)E.d_inst;
     const dim3 grid(E.grid_fuse), block(E.lanes_fuse);
+    ProfScope ps(E.prof, DOT_K_SWEEP, st);
     if (check)
       hipLaunchKernelGGL((kb_fuse<T, D, kMixed, false, true>), grid, block, 0, st, I, E.map_fuse, par);
     else if (rhs)
@@ -1258,9 +1264,8 @@ bool fuse_pays(int D, int precision, int count, int64_t nodes) {
   return D < 3 && nodes >= least;
 }
 
-// Whether an executor runs one-sweep iterations (kernel classes timed one by
-// one run as separate sweeps).
-bool one_sweep(const Exec& E) { return E.fused && !(E.prof && E.prof->cls >= 0); }
+// Whether an executor runs one-sweep iterations.
+bool one_sweep(const Exec& E) { return E.fused && !split_classes(E); }
 
 // Iteration `it` as a right-hand side (unless the previous sweep left it), the
 // transform passes and one sweep. alpha and beta are at place it & 1 before it
@@ -1288,7 +1293,7 @@ int fused_iter(const Exec& E, int it, hipStream_t st, bool more, Carry* cy) {
 }
 
 // Whether the executor runs the z-step beside the phi-step: needs the branch
-// streams, no kernel class being timed, no instance whose last axis takes the
+// streams, no class of the separate launches being timed, no instance whose last axis takes the
 // one-lane elimination (it keeps its checkpoints in W plane 0, which the
 // z-step writes), and at least kOverlapMinNodes grid nodes in all. The fork
 // and the join cost about 10 us per iteration; below that size the kernels
@@ -1299,7 +1304,7 @@ int fused_iter(const Exec& E, int it, hipStream_t st, bool more, Carry* cy) {
 // 1185 -> 1162 us; the 64-instance 2D batch 1154 -> 1086 us.
 constexpr int64_t kOverlapMinNodes = int64_t(1) << 21;
 bool overlapped(const Exec& E) {
-  return E.graphs && !E.fused && !(E.prof && E.prof->cls >= 0) && E.ntri_long == 0 && E.nodes >= kOverlapMinNodes;
+  return E.graphs && !E.fused && !split_classes(E) && E.ntri_long == 0 && E.nodes >= kOverlapMinNodes;
 }
 
 int branch_streams(GraphCache* g) {
@@ -1365,7 +1370,7 @@ int one_iter(const Exec& E, int it, hipStream_t st, hipStream_t side, bool more,
     return DOT_OK;
   }
   // kernel classes timed one by one run unfused
-  const bool timing = E.prof && E.prof->cls >= 0;
+  const bool timing = split_classes(E);
   bool rhs_ready = cy->rhs_ready, cone_ready = cy->cone_ready;
   if (!rhs_ready && !cone_ready && E.ntri_long == 0 && !timing) {
     if ((rc = launch_cone_rhs<T, D>(E, par, st))) return rc;
@@ -2641,7 +2646,7 @@ int dot_step_residuals_noalloc(dot_plan* P, const void* phi, const void* z, cons
 }
 
 int dot_profile_select(dot_plan* P, int32_t kernel_class) {
-  if (!P || kernel_class < -1 || kernel_class > DOT_K_RHS) return fail(DOT_EINVAL, "bad kernel class");
+  if (!P || kernel_class < -1 || kernel_class > DOT_K_PLANE) return fail(DOT_EINVAL, "bad kernel class");
   P->prof.cls = kernel_class;
   P->prof.used = 0;
   P->prof.ms = 0.0;
@@ -2898,7 +2903,7 @@ int dot_batch_autotune(dot_batch* B, void* ws, void* stream, dot_schedule* out) 
 }
 
 int dot_batch_profile_select(dot_batch* B, int32_t kernel_class) {
-  if (!B || kernel_class < -1 || kernel_class > DOT_K_RHS) return fail(DOT_EINVAL, "bad kernel class");
+  if (!B || kernel_class < -1 || kernel_class > DOT_K_PLANE) return fail(DOT_EINVAL, "bad kernel class");
   B->prof.cls = kernel_class;
   B->prof.used = 0;
   B->prof.ms = 0.0;

@@ -53,6 +53,10 @@ def kernel_bytes(D: int, n: Sequence[int], w: int) -> Dict[str, float]:
         # the fused launches with the next right-hand side (q_new counted once)
         "beta_rhs": beta + rhs - w * Q,
         "beta_cone_rhs": beta_cone + rhs - w * Q,
+        # one sweep: read phi, q, alpha, beta; write q, alpha, beta and the next right-hand side
+        "sweep": 8 * Nc + w * (2 * Q + 2 * K * S) + 2 * a * Q + w * Nc,
+        # the last two axes, forward and inverse: the work plane in and out (1D: phi at the end)
+        "plane": last_inv if D == 1 else 2 * w * Nc,
         # residual partials: read phi, q, alpha, beta
         "resid": w * (Q + K * S) + a * Q + 8 * Nc,
         "final": 0.0,
@@ -69,4 +73,9 @@ def iteration_min_bytes(D: int, n: Sequence[int], w: int) -> float:
 
 def launches_per_iteration(D: int) -> Dict[str, int]:
     return {"rhs": 1, "dct_first": 1, "dct_mid": max(D - 1, 0), "dct_last": 1, "dct_inv": D,
-            "cone": 1, "qd": 1, "beta": 1}
+            "cone": 1, "qd": 1, "beta": 1, "sweep": 1, "plane": 1}
+
+
+# Classes whose work a one-sweep iteration does in its sweep (the right-hand
+# side but after a residual check).
+SWEEP_CLASSES = ("rhs", "cone", "qd", "beta")
