@@ -325,7 +325,8 @@ int dot_test_fail_captures(int32_t count);
  * one that an autotune call found faster. */
 typedef struct {
   int32_t cw[4];       /* lines per tile, axes 0..D: 16, 32 or 64, also 4 or 8 on an eliminated last
-                          axis (set calls: 0 keeps the rule's) */
+                          axis (set calls: 0 keeps the rule's, or takes the next
+                          narrower that the waves given hold) */
   int32_t waves[4];    /* wavefronts per workgroup, 1..16, enough for the axis's work items
                           (set calls: 0 keeps the rule's for that tile width) */
   int32_t tuned;       /* out: 1 when the schedule was chosen by an autotune call */

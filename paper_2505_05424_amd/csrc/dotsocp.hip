@@ -2212,8 +2212,13 @@ int schedule_from(dot_plan* const* plans, int count, const dot_schedule* in, Sch
       Sched t;
       t.cw[a] = in->cw[a];
       const AxisGeom ag = axis_geom<T>(plans, count, a, t);
-      const int cw = ag.cw, w = in->waves[a] ? in->waves[a] : ag.waves;
-      if (!schedule_ok<T>(plans, count, a, cw, w, max_smem))
+      const int w = in->waves[a] ? in->waves[a] : ag.waves;
+      int cw = ag.cw;
+      auto ok = [&]() { return schedule_ok<T>(plans, count, a, cw, w, max_smem); };
+      // waves alone: they may be too few for the rule's tile and hold the work
+      // items of a narrower one (a narrow tile has half the accumulators)
+      while (!in->cw[a] && cw > kCWNarrow && !ok()) cw /= 2;
+      if (!ok())
         return fail(DOT_EINVAL, "axis " + std::to_string(a) + ": no launch of " + std::to_string(cw) +
                                     "-line tiles with " + std::to_string(w) + " waves for these instances");
       s.cw[a] = cw;
