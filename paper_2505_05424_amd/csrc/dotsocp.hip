@@ -1264,6 +1264,13 @@ bool fuse_pays(int D, int precision, int count, int64_t nodes) {
   return D < 3 && nodes >= least;
 }
 
+// Whether a call of max_iters iterations from count it0 takes one-sweep
+// iterations: where it does at least two of them. One alone would end at the
+// second places of alpha and beta, and copying those home costs more than the
+// sweep saves (calls of one iteration, us: 2D 64x256^2 FP64 separate 813, one
+// sweep 1103; with three the copy is paid back: 722 -> 664 per iteration).
+bool sweeps_pay(int it0, int max_iters) { return max_iters - (it0 & 1) >= 2; }
+
 // Whether an executor runs one-sweep iterations.
 bool one_sweep(const Exec& E) { return E.fused && !split_classes(E); }
 
@@ -1454,7 +1461,8 @@ int run_iters(const Exec& E, int it0, int max_iters, const void* ctl_dev, size_t
       if (!reinterpret_cast<const Ctl*>(static_cast<const char*>(ctl_host) + i * ctl_stride)->stop) return false;
     return true;
   };
-  if (E.graphs && E.graphs->fused != one_sweep(E)) {
+  // (a call too short for a graph leaves the captured ones to later calls)
+  if (E.graphs && max_iters >= kGraphIters && E.graphs->fused != one_sweep(E)) {
     drop_graph(*E.graphs);
     E.graphs->fused = one_sweep(E);
   }
@@ -1674,11 +1682,13 @@ struct RunF {
     HIP_OK(hipMemcpyAsync(P->host_ctl, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     HIP_OK(hipStreamSynchronize(st));
     const int it0 = P->host_ctl->iter;
-    if (fuse_pays(D, P->precision, 1, P->g.nb)) {
+    const bool sweeps = !P->host_ctl->stop && sweeps_pay(it0, max_iters) && fuse_pays(D, P->precision, 1, P->g.nb);
+    if (sweeps) {
       if (!P->fg.nblk) P->fg = fuse_shape(P->g);
       fuse_alloc(&P->fuse_ws, fuse_layout(P).bytes);
     }
     Exec E = plan_exec(P, 0);
+    E.fused = E.fused && sweeps;
     Inst<T> inst = state_inst<T>(P, state, ctl);
     if (E.fused) fuse_fields(inst, P, P->fg, P->fuse_ws);
     int rc = upload_inst(E, inst, st);
@@ -1936,6 +1946,7 @@ struct dot_batch {
   std::vector<char> active;    // instances laid out in the launch grids (empty: all)
   std::vector<FuseGeo> fg;     // one-sweep iterations of each instance
   void* fuse_ws = nullptr;     // their buffer (fuse_layout of each instance, one after another)
+  bool sweeps = false;         // the call that runs may take them (sweeps_pay)
   Prof prof;
   GraphCache graphs;
 };
@@ -2069,7 +2080,7 @@ template <typename T>
 int batch_descriptors(dot_batch* B, void* ws, hipStream_t st) {
   const int count = (int)B->plans.size();
   std::vector<Inst<T>> host(count);
-  B->E.fused = B->fuse_ws && B->E.grid_fuse;
+  B->E.fused = B->fuse_ws && B->E.grid_fuse && B->sweeps;
   size_t fuse_off = 0;
   uint32_t blk = 0, fblk = 0, plane = 0, line = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
@@ -2143,7 +2154,8 @@ struct BatchRunF {
     }
     std::vector<int> began(count);  // iteration counts at the start of the call
     for (int i = 0; i < count; ++i) began[i] = reinterpret_cast<const Ctl*>(hc + (size_t)i * B->ctl_stride)->iter;
-    if (B->E.grid_fuse) fuse_alloc(&B->fuse_ws, batch_fuse_bytes(B));
+    B->sweeps = sweeps_pay(B->it, max_iters);
+    if (B->E.grid_fuse && B->sweeps) fuse_alloc(&B->fuse_ws, batch_fuse_bytes(B));
     int rc = batch_compact<T>(B, ws, st, true);
     if (rc || (rc = batch_descriptors<T>(B, ws, st))) return rc;
     // the smallest time budget of the instances bounds the call
