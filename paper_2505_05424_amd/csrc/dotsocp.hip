@@ -779,9 +779,16 @@ void fuse_run(FuseGeo& f, const Geo& g, int tc) {
   f.nblk = f.ntile * (uint32_t)((g.N[0] + tc - 1) / tc);
 }
 // Cost of a round of workgroups per time slice, from measured launches: it
-// grows with the waves beside each other on a CU, since the launch is bound by
-// the bytes they move.
-double fuse_round(double waves_per_cu) { return 0.4 * waves_per_cu + 0.35; }
+// grows with the waves beside each other on a CU where the bytes they move
+// bound the launch, as in FP64; in mixed precision (half of them) the slices a
+// workgroup marches through count nearly alone. With one slope for both, mixed
+// runs got few waves and long marches (us per iteration, slope 0.4 -> 0.05:
+// 36x120^2 84.5 -> 76.9, against 81.8 with separate sweeps; 28x152x124 82.3 ->
+// 74.8, 250x75x35 89.8 -> 83.4, 1D 162x4000 200.6 -> 188.3; no other of 69
+// grids slower by more than 0.4%).
+double fuse_round(double waves_per_cu, int precision) {
+  return (precision == DOT_FP64 ? 0.4 : 0.05) * waves_per_cu + 0.35;
+}
 // A workgroup's time slices: two more than it owns, and its start.
 double fuse_slices(int tc) { return tc + 4.0; }
 // A short row of the box (contiguous nodes) costs more per node, for the
@@ -790,19 +797,20 @@ double fuse_row(const Geo& g, const FuseGeo& f) { return 1.0 + 4.0 / f.a[g.D]; }
 
 // Box and time run of the one-sweep iteration of one instance: the pair with
 // the fastest launch in that model, round by round (kFuseWaves waves are
-// resident per CU). 2D 64x256^2, mixed / FP64, us per iteration: boxes of 10x30
-// nodes over all 65 time nodes (234 workgroups, one round) 374 / 512, over 33
-// (two rounds) 389 / 558, 6x30x13 401 / 591, 9x30x65 (261 workgroups: a second
-// round for 5 of them) 515 / 667.
+// resident per CU). 2D 64x256^2, FP64 / mixed, us per iteration: the pick,
+// boxes of 11x37 nodes over 22 time nodes (504 workgroups of 8 waves, two full
+// rounds) 512 / 365; over 33 (336, the second round a third full) 585 / 420;
+// 10x30 over all 65 (234, one round) 513 / 385, over 33 520 / 392; 6x30 over
+// 13 551 / 388; 9x30 over 65 (261: a second round for 5 of them) 639 / 507.
 constexpr int kFuseCUs = 256, kFuseWaves = 8;
-FuseGeo fuse_shape(const Geo& g) {
+FuseGeo fuse_shape(const Geo& g, int precision) {
   const std::vector<int> runs = even_parts(g.N[0], g.N[0]);
   FuseGeo best{};
   double least = 0.0;
   for (FuseGeo f : fuse_boxes(g)) {
     const int waves = fuse_waves(f);
     const double room = (double)kFuseCUs * std::max(1, kFuseWaves / waves);
-    auto round_cost = [&](double blocks) { return fuse_round(waves * std::ceil(blocks / kFuseCUs)); };
+    auto round_cost = [&](double blocks) { return fuse_round(waves * std::ceil(blocks / kFuseCUs), precision); };
     for (int tc : runs) {
       fuse_run(f, g, tc);
       const double full = std::floor(f.nblk / room), rest = f.nblk - full * room;
@@ -824,7 +832,7 @@ FuseGeo fuse_shape(const Geo& g) {
 // average and the longest work per resident workgroup.
 constexpr int64_t kFuseWideNodes = int64_t(1) << 22;
 std::vector<FuseGeo> fuse_shapes(dot_plan* const* plans, int count) {
-  if (count == 1) return {fuse_shape(plans[0]->g)};
+  if (count == 1) return {fuse_shape(plans[0]->g, plans[0]->precision)};
   int64_t nodes = 0;
   int longest = 1;
   for (int i = 0; i < count; ++i) {
@@ -1249,15 +1257,22 @@ int launch_fuse(const Exec& E, int par, bool rhs, bool check, hipStream_t st) {
 // Whether a run over `nodes` grid nodes in all takes one-sweep iterations: from
 // the sizes where the bytes they save outweigh their longer chain per time
 // slice. us per iteration, separate sweeps -> one sweep; FP64: 2D 32x64^2 (0.14 M
-// nodes) 51.3 -> 53.3, 60x70x65 (0.29 M) 69.5 -> 67.7, 32x96^2 (0.31 M) 71.0 ->
-// 65.8, 64x256^2 (4.3 M) 697 -> 515, 32x1024^2 7395 -> 5313; mixed: 24x45x83
-// (0.10 M) 40.2 -> 46.2, 64x64x100 (0.43 M) 71.0 -> 74.2, 32x128^2 (0.55 M) 98.8 ->
-// 92.5, 64x256^2 449 -> 365, 32x1024^2 4582 -> 3443. Batches of small grids have
-// more halo: heterogeneous 2D batches, FP64: 5 members (1.0 M) 205 -> 208, 8
-// (1.8 M) 368 -> 341, 64 (11.5 M) 1823 -> 1418; mixed: 8 228 -> 245, 12 (2.4 M) 294 ->
-// 283, 64 1088 -> 972. In three dimensions the halo of a box that fits a
-// workgroup about doubles its cells (3D 32x64^3 mixed 1162 -> 1409): separate
-// sweeps.
+// nodes) 51.3 -> 53.3, 69x72x29 (0.15 M) 51.9 -> 54.4; of 11 grids from 2^18 nodes
+// to 0.41 M the least gain 1D 188x2116 (0.40 M) 126.8 -> 124.7, the largest
+// 27x189x75 (0.40 M) 85.1 -> 75.9; 64x256^2 (4.3 M) 675 -> 512, 32x1024^2 7259 ->
+// 5197. Mixed: 24x45x83 (0.10 M) 40.2 -> 46.2, 43x82x72 (0.27 M) 55.5 -> 62.5, 97x92x44
+// (0.41 M) 69.7 -> 72.6; 36x120^2 (0.54 M) 81.8 -> 76.9, 32x128^2 85.5 -> 80.6, 1D
+// 1000x540 165.5 -> 161.3, 64x256^2 447 -> 364, 32x1024^2 4407 -> 3283; of 44 mixed grids
+// of 0.44 to 7 M two lose, 205x86x96 174.8 -> 177.7 and 296x160x36 177.7 -> 178.9.
+// Batches share one
+// workgroup size and have more halo. FP64, from 5 * 2^18: least gain 8 of 64^3
+// (2.2 M) 321 -> 304, most 24 heterogeneous members (7.1 M) 1125 -> 922; below,
+// 27 of 32^3 (0.97 M) 128 -> 136, 5 heterogeneous (1.0 M) 205 -> 208. Mixed, from
+// 2^21: least 8 heterogeneous (2.4 M) 287 -> 281, most 183 of 1D 64x200 (2.4 M) 202
+// -> 166; below, 6 of 64^3 (1.6 M) 144 -> 160, 5 of 32x100^2 (1.7 M) 158 -> 172, 5
+// heterogeneous (1.9 M) 197 -> 211. In three dimensions the halo of a box that
+// fits a workgroup about doubles its cells (3D 32x64^3 mixed 1162 -> 1409):
+// separate sweeps.
 bool fuse_pays(int D, int precision, int count, int64_t nodes) {
   const int64_t least = precision == DOT_FP64 ? (count == 1 ? int64_t(1) << 18 : int64_t(5) << 18)
                                               : (count == 1 ? int64_t(1) << 19 : int64_t(1) << 21);
@@ -1684,7 +1699,7 @@ struct RunF {
     const int it0 = P->host_ctl->iter;
     const bool sweeps = !P->host_ctl->stop && sweeps_pay(it0, max_iters) && fuse_pays(D, P->precision, 1, P->g.nb);
     if (sweeps) {
-      if (!P->fg.nblk) P->fg = fuse_shape(P->g);
+      if (!P->fg.nblk) P->fg = fuse_shape(P->g, P->precision);
       fuse_alloc(&P->fuse_ws, fuse_layout(P).bytes);
     }
     Exec E = plan_exec(P, 0);
