@@ -283,9 +283,9 @@ kb_tri_part(const Inst<T>* __restrict__ I, const uint16_t* __restrict__ map, int
 
 // ---- step-level kernels (single instance, caller pointers) ----------------
 
-// Zero n 32-bit words (one workgroup).
-__global__ void __launch_bounds__(256) kb_clear_words(uint32_t* __restrict__ p, int n) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
+// Zero n 32-bit words.
+__global__ void __launch_bounds__(256) kb_clear_words(uint32_t* __restrict__ p, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
 template <typename T, int D>

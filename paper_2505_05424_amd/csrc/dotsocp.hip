@@ -1655,20 +1655,30 @@ Exec plan_exec(dot_plan* P, int slot) {
   return E;
 }
 
-// The buffer of the one-sweep iterations, allocated and cleared at the first
-// run (entries outside a plane's set are copied home with it and must be
-// zero). Without the memory for it the separate sweeps run instead, with the
-// same results; the next run asks again.
-void fuse_alloc(void** ws, size_t bytes) {
-  if (*ws) return;
+// The buffer of the one-sweep iterations, allocated by the first run that takes
+// them; true when this call did. Without the memory for it the separate sweeps
+// run instead, with the same results; the next run asks again. Other threads
+// may be capturing and other streams running: nothing here waits for the device
+// or uses the default stream.
+bool fuse_alloc(void** ws, size_t bytes) {
+  if (*ws) return false;
   DevLock lk(g_dev_mu);
-  if (hipMalloc(ws, bytes) != hipSuccess) {
-    *ws = nullptr;
-  } else if (hipMemset(*ws, 0, bytes) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-    (void)hipFree(*ws);
-    *ws = nullptr;
-  }
-  if (!*ws) (void)hipGetLastError();
+  if (hipMalloc(ws, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  *ws = nullptr;
+  return false;
+}
+
+// Clears the second place of alpha in the buffer of one instance: the entries
+// outside a plane's set, which nothing writes, are copied home with the others
+// and must be zero. (beta goes home cell by cell; the rest is written before it
+// is read.)
+int fuse_clear(const dot_plan* P, void* ws, hipStream_t st) {
+  const size_t words = (size_t)(P->D + 1) * P->g.nb * (sizeof(double) / sizeof(uint32_t));
+  hipLaunchKernelGGL(kb_clear_words, dim3((unsigned)std::min<size_t>(2048, (words + 255) / 256)), dim3(256), 0, st,
+                     at<uint32_t>(ws, fuse_layout(P).alpha), words);
+  HIP_OK(hipGetLastError());
+  return DOT_OK;
 }
 
 // alpha and beta of an instance that did an odd number of one-sweep iterations
@@ -1700,7 +1710,10 @@ struct RunF {
     const bool sweeps = !P->host_ctl->stop && sweeps_pay(it0, max_iters) && fuse_pays(D, P->precision, 1, P->g.nb);
     if (sweeps) {
       if (!P->fg.nblk) P->fg = fuse_shape(P->g, P->precision);
-      fuse_alloc(&P->fuse_ws, fuse_layout(P).bytes);
+      if (fuse_alloc(&P->fuse_ws, fuse_layout(P).bytes)) {
+        const int rc = fuse_clear(P, P->fuse_ws, st);
+        if (rc) return rc;
+      }
     }
     Exec E = plan_exec(P, 0);
     E.fused = E.fused && sweeps;
@@ -1870,7 +1883,7 @@ struct ResidNoAllocF {
     // memset keeps the call capturable. Every partial slot of every workgroup
     // is written by the two sweeps below, so the partial rows need no clearing.
     hipLaunchKernelGGL(kb_clear_words, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(ctl),
-                       (int)(sizeof(Ctl) / sizeof(uint32_t)));
+                       sizeof(Ctl) / sizeof(uint32_t));
     HIP_OK(hipGetLastError());
     int rc = upload_inst(E, inst_of<T>(P, (double*)phi, (T*)nullptr, (T*)q, (T*)nullptr, (double*)alpha, (T*)beta,
                                        (T*)nullptr, (double*)nullptr, ctl, partials),
@@ -2170,7 +2183,14 @@ struct BatchRunF {
     std::vector<int> began(count);  // iteration counts at the start of the call
     for (int i = 0; i < count; ++i) began[i] = reinterpret_cast<const Ctl*>(hc + (size_t)i * B->ctl_stride)->iter;
     B->sweeps = sweeps_pay(B->it, max_iters);
-    if (B->E.grid_fuse && B->sweeps) fuse_alloc(&B->fuse_ws, batch_fuse_bytes(B));
+    if (B->E.grid_fuse && B->sweeps && fuse_alloc(&B->fuse_ws, batch_fuse_bytes(B))) {
+      size_t off = 0;
+      for (const dot_plan* P : B->plans) {
+        const int rc = fuse_clear(P, static_cast<char*>(B->fuse_ws) + off, st);
+        if (rc) return rc;
+        off += align256(fuse_layout(P).bytes);
+      }
+    }
     int rc = batch_compact<T>(B, ws, st, true);
     if (rc || (rc = batch_descriptors<T>(B, ws, st))) return rc;
     // the smallest time budget of the instances bounds the call
