@@ -42,12 +42,21 @@
  *
  * Ownership: the caller owns every buffer it passes; the library keeps no
  * pointer to caller memory after a call returns. A dot_plan owns small
- * constant tables on its device (transform matrices, eigenvalues, weights;
- * with few last-axis lines of more than 576 nodes also the pivots of their
- * elimination, one double plane of at most some 40 MB) and, from its first dot_run on a large 1D or 2D grid, a buffer of D+3 double
- * planes that its iterations use beside the state (about a sixth of the
- * state; a batch holds one for its members). Where the device has no memory
- * left for it, runs take the launches of smaller grids: slower, same results.
+ * constant tables on its device (transform matrices, eigenvalues, weights) and
+ * two things that only speed depends on:
+ *   - with few last-axis lines of more than 576 nodes, the pivots of their
+ *     elimination: one double plane, at most some 40 MB, from its creation. A
+ *     batch and a serving context hold them for the members or requests that
+ *     are running, where their launches use them: some 40 MB in all.
+ *   - from the first dot_run of two or more iterations on a large 1D or 2D grid,
+ *     a buffer that its iterations use beside the state, until it is destroyed
+ *     (a batch: one for its members). Double planes of NB entries: D+3 in
+ *     DOT_FP64, D+2 in DOT_MIXED; and where the last axis has more than 576
+ *     nodes, one double per 32 nodes of it. In 2D that is 17% of a DOT_FP64
+ *     state and 23% of a DOT_MIXED one, in 1D 22% and 26%.
+ * Neither is part of dot_footprint_bytes or of a context's budget. Without the
+ * memory for one, runs take the launches that do not need it: slower, same
+ * results.
  * Streams are hipStream_t passed as void*; NULL means the default stream.
  * All step functions are asynchronous on that stream.
  */
@@ -305,6 +314,10 @@ int dot_batch_set_graphs(dot_batch* batch, int32_t enable);
 /* Testing the fallback above: the next `count` graph captures in this
  * process fail before they start (0 clears; DOT_EINVAL if negative). */
 int dot_test_fail_captures(int32_t count);
+/* Testing runs without the memory of the one-sweep buffer and of the pivots
+ * (see Ownership): the next `count` allocations of either in this process fail
+ * (0 clears; DOT_EINVAL if negative). */
+int dot_test_fail_scratch(int32_t count);
 
 /* ---- transform schedules and their autotuner ----------------------------- */
 /* The cosine-transform passes of the phi-step (Sec. 4, the Poisson solve of

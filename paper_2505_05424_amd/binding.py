@@ -36,7 +36,7 @@ EXPORTED = [
     "dot_footprint_bytes", "dot_ctx_create", "dot_ctx_destroy", "dot_ctx_submit", "dot_ctx_submit_ml", "dot_ctx_step", "dot_ctx_poll",
     "dot_ctx_fetch", "dot_ctx_stats", "dot_coarsen_data", "dot_prolong", "dot_solve_multilevel",
     "dot_step_residuals_noalloc", "dot_ctx_export", "dot_ctx_import", "dot_ctx_last_error", "dot_batch_promote",
-    "dot_ctx_keep_capped", "dot_batch_promote_member", "dot_test_fail_captures",
+    "dot_ctx_keep_capped", "dot_batch_promote_member", "dot_test_fail_captures", "dot_test_fail_scratch",
 ]
 NOALLOC_SCRATCH_BYTES = 8 << 20
 
@@ -173,6 +173,7 @@ def load(path: Optional[str] = None) -> ctypes.CDLL:
     lib.dot_plan_set_graphs.argtypes = [vp, i32]
     lib.dot_batch_set_graphs.argtypes = [vp, i32]
     lib.dot_test_fail_captures.argtypes = [i32]
+    lib.dot_test_fail_scratch.argtypes = [i32]
     for fn in ("dot_plan_set_schedule", "dot_batch_set_schedule", "dot_plan_get_schedule",
                "dot_batch_get_schedule"):
         getattr(lib, fn).argtypes = [vp, ctypes.POINTER(dot_schedule)]
@@ -385,6 +386,12 @@ def dot_test_fail_captures(count: int):
     """The next `count` graph captures fail before they start (testing the
     fallback to plain launches)."""
     _check(load().dot_test_fail_captures(int(count)))
+
+
+def dot_test_fail_scratch(count: int):
+    """The next `count` allocations of the one-sweep buffer or of pivots fail
+    (testing the launches that do without)."""
+    _check(load().dot_test_fail_scratch(int(count)))
 
 
 def dot_batch_set_graphs(batch, enable: bool):

@@ -50,6 +50,14 @@ using DevLock = std::lock_guard<std::recursive_mutex>;
 
 // Captures still to fail on purpose (dot_test_fail_captures).
 std::atomic<int> g_fail_captures{0};
+// The same for the device memory that only speed depends on (dot_test_fail_scratch).
+std::atomic<int> g_fail_scratch{0};
+
+bool take_failure(std::atomic<int>& left) {
+  for (int f = left.load(); f > 0;)
+    if (left.compare_exchange_weak(f, f - 1)) return true;
+  return false;
+}
 
 int fail(int code, const std::string& msg) {
   g_err = msg;
@@ -193,7 +201,7 @@ struct dot_plan {
   bool wide_ok[kMaxAxes] = {true, true, true, true};  // the axis fits a tile of kCW lines
   bool mid_ok[kMaxAxes] = {true, true, true, true};   // the axis fits a tile of kCWMid lines
   bool tri = false;      // the last axis is solved by tridiagonal elimination
-  double* piv = nullptr;    // pivots of the last axis's lines, where line_pays
+  double* piv = nullptr;    // pivots of the last axis's lines, where launches take the long-line solve
   void* step_cbuf = nullptr;  // c' plane of the tridiagonal solve for step-level calls
   Sched sched;                // transform schedule of this plan's own launches
   // device constant tables
@@ -581,7 +589,7 @@ LineGeom line_geom(dot_plan* const* plans, int count, const Sched& s) {
   for (int i = 0; i < count; ++i) {
     const dot_plan* P = plans[i];
     if (!line_long(P)) continue;
-    if (!P->piv || !s.rule()) return LineGeom();
+    if (!line_pays(P->lines[P->D], P->g.N[P->D]) || !s.rule()) return LineGeom();
     ++lg.insts;
     lines += P->lines[P->D];
     row = std::max(row, tri_line_bytes(P->g.N[P->D]));
@@ -593,20 +601,48 @@ LineGeom line_geom(dot_plan* const* plans, int count, const Sched& s) {
     if (line_long(plans[i])) lg.blocks += tiles_for(plans[i]->lines[plans[i]->D], lg.cw);
   return lg.blocks <= kLineBlocks ? lg : LineGeom();
 }
-// The pivots of a plan. Without the memory for them the chunked solve runs.
+// Device memory that only speed depends on; null without it.
+void* scratch_alloc(size_t bytes) {
+  void* p = nullptr;
+  if (!take_failure(g_fail_scratch) && hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+// The pivots of a plan, built on `st` and complete on return. Without the
+// memory for them the chunked solve runs.
 template <typename T>
-int build_pivots(dot_plan* P) {
-  const int64_t lines = P->g.nb / P->g.N[P->D];
-  if (hipMalloc((void**)&P->piv, (size_t)P->g.nb * sizeof(double)) != hipSuccess) {
-    (void)hipGetLastError();
-    P->piv = nullptr;
-    return DOT_OK;
-  }
-  hipLaunchKernelGGL((kb_tri_pivots<T>), dim3((unsigned)((lines + 63) / 64)), dim3(64), 0, nullptr, P->g,
+int build_pivots(dot_plan* P, hipStream_t st) {
+  const int64_t lines = P->lines[P->D];
+  P->piv = static_cast<double*>(scratch_alloc((size_t)P->g.nb * sizeof(double)));
+  if (!P->piv) return DOT_OK;
+  hipLaunchKernelGGL((kb_tri_pivots<T>), dim3((unsigned)((lines + 63) / 64)), dim3(64), 0, st, P->g,
                      (const T*)P->lam_other, P->piv);
   HIP_OK(hipGetLastError());
-  HIP_OK(hipStreamSynchronize(nullptr));
+  HIP_OK(hipStreamSynchronize(st));
   return DOT_OK;
+}
+void drop_pivots(dot_plan* P) {
+  if (!P->piv) return;
+  DevLock lk(g_dev_mu);
+  (void)hipFree(P->piv);
+  P->piv = nullptr;
+}
+
+// Pivots for the long-line solve `lg` over plans[0..count), which a batch or a
+// serving context asks for when its launches take that solve: a plan of its
+// own holds them from its creation, but members and requests wait, stop or
+// share launches that take the chunked solve. So they hold no more than one
+// launch reads (some 40 MB). False if one is missing.
+bool line_pivots(dot_plan* const* plans, int count, const LineGeom& lg, hipStream_t st) {
+  bool all = true;
+  for (int i = 0; i < count && lg.insts && all; ++i) {
+    dot_plan* P = plans[i];
+    if (!line_long(P) || P->piv) continue;
+    const int rc = P->precision == DOT_FP64 ? build_pivots<double>(P, st) : build_pivots<float>(P, st);
+    all = rc == DOT_OK && P->piv;
+  }
+  return all;
 }
 
 // Schedules of axis a that every instance of a launch can take: the tile
@@ -1418,8 +1454,7 @@ int one_iter(const Exec& E, int it, hipStream_t st, hipStream_t side, bool more,
 template <typename T, int D>
 int capture_block(const Exec& E, int it, hipGraphExec_t* out, int n = kGraphIters) {
   DevLock lk(g_dev_mu);
-  for (int f = g_fail_captures.load(); f > 0;)
-    if (g_fail_captures.compare_exchange_weak(f, f - 1)) return fail(DOT_EDEVICE, "capture failed on purpose (test)");
+  if (take_failure(g_fail_captures)) return fail(DOT_EDEVICE, "capture failed on purpose (test)");
   Exec Ec = E;
   Ec.prof = nullptr;  // no events inside a captured graph
   if (!E.graphs->cap) HIP_OK(hipStreamCreateWithFlags(&E.graphs->cap, hipStreamNonBlocking));
@@ -1645,7 +1680,7 @@ Exec plan_exec(dot_plan* P, int slot) {
     E.waves_axis[a] = ag.waves;
   }
   set_plane(E, plane_geom(&P, 1, P->sched), nullptr);
-  set_line(E, line_geom(&P, 1, P->sched), nullptr);
+  set_line(E, P->piv ? line_geom(&P, 1, P->sched) : LineGeom(), nullptr);
   E.fused = slot == 0 && P->fuse_ws && P->fg.nblk;
   E.grid_fuse = P->fg.nblk;
   E.lanes_fuse = fuse_waves(P->fg) * 64;
@@ -1663,10 +1698,8 @@ Exec plan_exec(dot_plan* P, int slot) {
 bool fuse_alloc(void** ws, size_t bytes) {
   if (*ws) return false;
   DevLock lk(g_dev_mu);
-  if (hipMalloc(ws, bytes) == hipSuccess) return true;
-  (void)hipGetLastError();
-  *ws = nullptr;
-  return false;
+  *ws = scratch_alloc(bytes);
+  return *ws != nullptr;
 }
 
 // Clears the second place of alpha in the buffer of one instance: the entries
@@ -2021,7 +2054,8 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
   if (pg.steps)
     for (int k = 0; k < n; ++k) maps.insert(maps.end(), (size_t)plane_count(plans[k]), (uint16_t)idx[k]);
   const size_t line_off = maps.size();
-  const LineGeom lg = line_geom(plans.data(), n, s);
+  LineGeom lg = line_geom(plans.data(), n, s);
+  if (!line_pivots(plans.data(), n, lg, nullptr)) lg = LineGeom();
   for (int k = 0; k < n && lg.insts; ++k)
     if (line_long(plans[k]))
       maps.insert(maps.end(), (size_t)tiles_for(plans[k]->lines[B->D], lg.cw), (uint16_t)idx[k]);
@@ -2050,6 +2084,8 @@ int batch_layout(dot_batch* B, const Sched& s, const std::vector<char>* act = nu
     HIP_OK(hipDeviceSynchronize());  // no launch of the old layout is still reading its maps
     (void)hipFree(B->d_maps);
   }
+  for (int i = 0; i < count; ++i)
+    if (!lg.insts || !(on.empty() || on[i])) drop_pivots(B->plans[i]);
   B->d_maps = fresh;
   B->sched = s;
   B->active = on;
@@ -2469,7 +2505,8 @@ void dot_plan_destroy(dot_plan* P) {
   delete P;
 }
 
-int dot_plan_create(const dot_problem* p, dot_plan** out) {
+// pivots: the plan runs by itself (not as a member of a batch or a request)
+static int plan_create(const dot_problem* p, dot_plan** out, bool pivots) {
   DevLock lk(g_dev_mu);
   if (!out) return fail(DOT_EINVAL, "null output pointer");
   *out = nullptr;
@@ -2555,8 +2592,8 @@ int dot_plan_create(const dot_problem* p, dot_plan** out) {
   }
   rc = P->precision == DOT_FP64 ? build_eigs<double>(P.get()) : build_eigs<float>(P.get());
   if (rc) return rc;
-  if (line_long(P.get()) && line_pays(P->lines[D], g.N[D])) {
-    rc = P->precision == DOT_FP64 ? build_pivots<double>(P.get()) : build_pivots<float>(P.get());
+  if (pivots && line_long(P.get()) && line_pays(P->lines[D], g.N[D])) {
+    rc = P->precision == DOT_FP64 ? build_pivots<double>(P.get(), nullptr) : build_pivots<float>(P.get(), nullptr);
     if (rc) return rc;
   }
   const size_t pb = (size_t)g.nb * P->scalar_bytes;
@@ -2587,6 +2624,8 @@ int dot_plan_create(const dot_problem* p, dot_plan** out) {
   *out = P.release();
   return DOT_OK;
 }
+
+int dot_plan_create(const dot_problem* p, dot_plan** out) { return plan_create(p, out, true); }
 
 int dot_plan_get_info(const dot_plan* P, dot_plan_info* o) {
   if (!P || !o) return fail(DOT_EINVAL, "null argument");
@@ -2721,6 +2760,12 @@ int dot_test_fail_captures(int32_t count) {
   return DOT_OK;
 }
 
+int dot_test_fail_scratch(int32_t count) {
+  if (count < 0) return fail(DOT_EINVAL, "count must be >= 0");
+  g_fail_scratch.store(count);
+  return DOT_OK;
+}
+
 int dot_plan_set_graphs(dot_plan* P, int32_t enable) {
   if (!P) return fail(DOT_EINVAL, "null plan");
   P->graphs.enabled = enable != 0;
@@ -2782,7 +2827,7 @@ int dot_batch_create(const dot_problem* probs, int32_t count, dot_batch** out) {
   }
   for (int i = 0; i < count; ++i) {
     dot_plan* P = nullptr;
-    int rc = dot_plan_create(&probs[i], &P);
+    int rc = plan_create(&probs[i], &P, false);
     if (rc) return fail(rc, "problem " + std::to_string(i) + ": " + g_err);
     B->plans.push_back(P);
   }
@@ -3569,7 +3614,10 @@ int ctx_rebuild(dot_ctx* C, hipStream_t st) {
   }
   // descriptors of the active instances, in slot order
   const PlaneGeom pg = plane_geom(act.data(), (int)act.size(), Sched());
-  const LineGeom lg = line_geom(act.data(), (int)act.size(), Sched());
+  LineGeom lg = line_geom(act.data(), (int)act.size(), Sched());
+  if (!line_pivots(act.data(), (int)act.size(), lg, st)) lg = LineGeom();
+  if (!lg.insts)
+    for (dot_plan* P : act) drop_pivots(P);  // no step is running
   uint32_t blk = 0, plane = 0, line = 0;
   uint32_t tile[kMaxAxes] = {0, 0, 0, 0};
   int idx = 0;
@@ -3733,6 +3781,7 @@ int ctx_retire(dot_ctx* C, hipStream_t st) {
       HIP_OK(hipMemcpyAsync(reinterpret_cast<char*>(C->d_ctl) + (size_t)sl * C->ctl_stride, &h, sizeof(Ctl),
                             hipMemcpyHostToDevice, st));
       HIP_OK(hipStreamSynchronize(st));
+      drop_pivots(Pc);
       r->level += 1;
       r->plan = Pf;
       r->off = r->block + r->lvl_off[r->level];
@@ -3753,6 +3802,7 @@ int ctx_retire(dot_ctx* C, hipStream_t st) {
       r->final_ck.resize(checkpoint_bytes(r));
       if ((rc = write_checkpoint(C, r, r->final_ck.data(), st))) return rc;
     }
+    drop_pivots(P);
     r->status = kDone;
     C->arena.release(r->block, r->bytes);
     C->slots[sl] = nullptr;
@@ -3883,7 +3933,7 @@ int ctx_submit_impl(dot_ctx* C, const dot_problem* p, int32_t levels, uint64_t* 
     const int v = levels - l;  // coarse level v: max{tol 10^-v, 1e-6}
     if (v > 0) q.tol = std::max(p->tol * std::pow(10.0, -v), 1e-6);
     dot_plan* P = nullptr;
-    rc = dot_plan_create(&q, &P);
+    rc = plan_create(&q, &P, false);
     if (rc) return rc;
     r->plans.push_back(P);
     r->lvl_off.push_back(total);
