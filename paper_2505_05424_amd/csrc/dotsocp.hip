@@ -516,16 +516,24 @@ AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
 // (us per iteration, passes -> plane solve): the launches that it saves are
 // all there is to gain, so it holds while the planes are solved in at most two
 // rounds over the CUs, of which each holds one FP64 plane or two FP32 ones
-// (FP64 400x20^2 84.8 -> 80.5, 20^4 71.4 -> 67.2, 1D 16x32 23.7 -> 17.3;
-// 12x40x27x31, 533 planes, 112.8 -> 112.7, 900x15^2 217.9 -> 221.8; mixed 67.4
-// -> 61.3, 62.8 -> 56.3, 23.8 -> 16.9, 90.8 -> 88.2; more than 512 only of 640
-// points: 900x64^2 506.6 -> 491.2, but 20x40x10^2, 861 planes, 52.2 -> 53.7)
-// and, in FP64, up to 4096 points, past which a wave takes a second line block
-// (32x63^2 47.7 -> 45.5, 64x32x64 51.4 -> 47.8, but 32x64^2 51.4 -> 54.6; mixed
-// 43.7 -> 38.2, 44.9 -> 38.8, 46.2 -> 43.4).
+// (FP64 400x20^2 84.8 -> 80.5, 20^4 71.4 -> 67.2, 1D 16x32 23.7 -> 17.3, 499x40x24,
+// 500 planes, 131.5 -> 127.3; 518x9x26, 519 planes, 107.2 -> 108.4, 637x3x68 128.0 ->
+// 135.1; mixed 67.4 -> 61.3, 62.8 -> 56.3, 23.8 -> 16.9, 500 planes of 560 points 86.3
+// -> 79.5; past 1024 planes 24x52x13x29 99.2 -> 104.2). Mixed from 513 to 1024 planes,
+// of which two share a CU in both rounds: each of 10 grids of 640 points and more
+// gains (639x40x16 112.3 -> 108.6, 822x45x20 162.6 -> 161.0), 6 of 25 smaller ones
+// lose (30x29x6x17, 126 points, 52.1 -> 52.9, 902x8x70, 639 points, 170.7 -> 172.1).
+// In FP64 up to 4096 points (32x63^2 47.7 -> 45.5, but 32x64^2 51.4 -> 54.6;
+// mixed 43.7 -> 38.2, 46.2 -> 43.4), and where a wave has two line blocks (an axis of
+// 66 points and more beside one of more than 32, or of 65 beside more than 48),
+// whose second product only many planes pay for, from 64 planes: 1D 66x55 26.3 ->
+// 30.0, 17x68x51 41.8 -> 44.5, 32x57x69 48.4 -> 50.9, 62x51x64 56.4 -> 56.9; 63x68x50
+// 59.2 -> 58.3, 101x44x65 70.5 -> 66.0. FP32 products are short enough (of 40 such
+// grids only 1D 68x53 loses, 26.0 -> 26.2, most gain 3 to 10%).
 constexpr int64_t kPlaneCount = 512;
 constexpr int kPlanePoints64 = 4096;
 constexpr int kPlanePointsTwo = 640;
+constexpr int64_t kPlaneCountTwoBlocks64 = 64;
 struct PlaneGeom {
   int steps = 0;
   int64_t blocks = 0;
@@ -550,10 +558,13 @@ PlaneGeom plane_geom(dot_plan* const* plans, int count, const Sched& s) {
   const bool twice = plans[0]->precision != DOT_FP64 && least >= kPlanePointsTwo;
   if (pg.blocks > (twice ? 2 : 1) * kPlaneCount) return PlaneGeom();
   pg.steps = longest > 64 ? 9 : 8;
+  int items = 1;
   for (int i = 0; i < count; ++i) {
     const int N1 = plans[i]->g.N[plans[i]->D - 1], N2 = plans[i]->g.N[plans[i]->D];
-    if (plane_blocks(N1, N2) > plane_items(pg.steps) || plane_blocks(N2, N1) > plane_items(pg.steps)) return PlaneGeom();
+    items = std::max({items, plane_blocks(N1, N2), plane_blocks(N2, N1)});
   }
+  if (items > plane_items(pg.steps)) return PlaneGeom();
+  if (items > 1 && plans[0]->precision == DOT_FP64 && pg.blocks < kPlaneCountTwoBlocks64) return PlaneGeom();
   return pg;
 }
 

@@ -12,13 +12,16 @@ pytestmark = pytest.mark.gpu
 
 D64, MIX = B.DOT_FP64, B.DOT_MIXED
 # grid, precision, taken?
-CASES = [((64, 62), D64, True), ((55, 71), D64, True), ((3, 55, 71), D64, True), ((2, 2, 71, 55), D64, True),
-         ((511, 6, 9), D64, True), ((15, 31, 20, 9), D64, True),
+CASES = [((63, 63), D64, True), ((71, 31), D64, True), ((17, 65), D64, True), ((4, 71, 31), D64, True),
+         ((2, 2, 24, 71), D64, True), ((511, 6, 9), D64, True), ((15, 31, 20, 9), D64, True),
+         # two line blocks in a wave
+         ((63, 68, 50), D64, True), ((7, 7, 60, 66), D64, True), ((63, 64, 61), D64, True),
+         ((62, 68, 50), D64, False), ((6, 8, 60, 66), D64, False), ((66, 55), D64, False), ((64, 62), D64, False),
          ((64, 64), MIX, True), ((5, 71, 63), MIX, True), ((511, 4, 6), MIX, True), ((1023, 25, 25), MIX, True),
          ((30, 32, 40, 16), MIX, True),
-         ((64, 64), D64, False), ((2, 2, 71, 62), D64, False), ((512, 6, 9), D64, False), ((3, 72, 20), D64, False),
-         ((12, 40, 27, 31), D64, False), ((72, 40), MIX, False), ((5, 71, 64), MIX, False), ((1024, 25, 25), MIX, False),
-         ((512, 4, 6), MIX, False)]
+         ((100, 64, 64), D64, False), ((2, 2, 71, 62), D64, False), ((512, 6, 9), D64, False),
+         ((3, 72, 20), D64, False), ((12, 40, 27, 31), D64, False), ((72, 40), MIX, False), ((5, 71, 64), MIX, False),
+         ((1024, 25, 25), MIX, False), ((512, 4, 6), MIX, False)]
 
 
 def _run(plan, its):
