@@ -430,16 +430,23 @@ int pass_waves(int L, int64_t tiles, int cw, size_t smem, bool last) {
 // tiles that share a CU (or four); else the narrow one. Measured (us per
 // iteration, 16 against 32 lines): 48x150x131 FP64 axis 1, 203 tiles of 32,
 // 139.9 / 137.1 and mixed 106.0 / 101.6; 32x200x180 FP64 axis 1, 187 tiles,
-// 191.9 / 185.5; 40x120x70 FP64 last axis, 156 tiles, 71.4 / 70.1, but axis 1,
-// 91 tiles, 71.6 / 73.4; 64x256^2 FP64 axis 1, 523 tiles of which two fit a
-// CU, 510.8 / 512.5.
+// 191.9 / 185.5; 40x120x70 FP64 last axis, 156 tiles, 71.4 / 70.1; 64x256^2 FP64
+// axis 1, 523 tiles of which two fit a CU, 510.8 / 512.5. Below 150 tiles the
+// narrow one wins the more the fewer there are (19x180x128 FP64 axis 1, 81 tiles,
+// 82.1 / 86.5; 114x156x22 axis 0, 113, 76.0 / 78.8; but 120x38x111 axis 0, 137, 90.1 /
+// 87.6). Up to 256 tiles an axis other than the last takes the middle width only
+// with its neighbour (`paired`): passes of different widths one after the other
+// cost more than the coefficients save, or nothing is saved (16 on both against
+// 32 on the one: 46x24x153 FP64 axis 1 57.0 / 59.2, 44x28x123 52.6 / 54.4, 53x49x31x1 axis 2
+// 70.8 / 72.3 and mixed 62.0 / 64.6, 28x57x18x3 61.5 / 62.9 and 55.5 / 56.9; 32 on both: 13x41x47x11
+// FP64 95.4 / 92.2, mixed 80.5 / 76.2).
 constexpr int64_t kWideTiles = 4 * kPassCUs;
 constexpr int64_t kMidTiles = 150;
 constexpr size_t kMidLds = 40 << 10;
-int choose_cw(int64_t lines, bool wide_ok, bool mid_ok, size_t mid_smem) {
+int choose_cw(int64_t lines, bool wide_ok, bool mid_ok, size_t mid_smem, bool paired) {
   if (wide_ok && (lines + kCW - 1) / kCW >= kWideTiles) return kCW;
   const int64_t mid = (lines + kCWMid - 1) / kCWMid;
-  if (mid_ok && mid >= kMidTiles &&
+  if (mid_ok && mid >= (paired ? kMidTiles : kPassCUs) &&
       (mid_smem <= kMidLds || (mid + kPassCUs - 1) / kPassCUs <= (int64_t)(kPassLds / mid_smem)))
     return kCWMid;
   return kCWNarrow;
@@ -472,13 +479,14 @@ int64_t tiles_for(int64_t lines, int cw) { return (lines + cw - 1) / cw; }
 // else from the rules above (a last axis that every instance solves by
 // elimination takes one round of the partitioned solve: 8 lines of up to 288
 // nodes, 4 of up to 576 per 256 lanes; 64 for longer lines), and the LDS bytes.
+// alone: whatever the neighbouring axes take.
 struct AxisGeom {
   int cw = kCW, waves = 4;
   int64_t tiles = 0;
   size_t smem = 0;
 };
 template <typename T>
-AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
+AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s, bool alone = false) {
   int64_t all_lines = 0;
   bool wide_ok = true, mid_ok = true, all_tri = true;
   const bool last = a == plans[0]->D;
@@ -495,10 +503,14 @@ AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s) {
     mid_ok = mid_ok && plans[i]->mid_ok[a];
     all_tri = all_tri && plans[i]->tri;
   }
+  auto paired = [&]() {  // the neighbour by its own lines (`alone`)
+    return alone || last || plans[0]->D == 1 ||
+           axis_geom<T>(plans, count, a == 0 ? 1 : a - 1, Sched(), true).cw > kCWNarrow;
+  };
   AxisGeom ag;
   ag.cw = s.cw[a] ? s.cw[a]
                   : ((last && all_tri) ? tri_default_cw(plans, count)
-                                       : choose_cw(all_lines, wide_ok, mid_ok, smem(kCWMid)));
+                                       : choose_cw(all_lines, wide_ok, mid_ok, smem(kCWMid), paired()));
   for (int i = 0; i < count; ++i) ag.tiles += tiles_for(plans[i]->lines[a], ag.cw);
   ag.smem = smem(ag.cw);
   int waves = 1;
