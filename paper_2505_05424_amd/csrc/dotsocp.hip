@@ -394,15 +394,21 @@ int64_t pass_per_cu(int64_t tiles, size_t smem) {
 // Waves per workgroup of a transform pass. A CU holds 16 waves of the FP64
 // kernels (124 registers) and 20 of the FP32 ones (86), so the workgroups that
 // should share a CU get an equal part of those: one takes a wave per work item
-// and a few more for the loads, two take eight, up to four take four. With
-// more, smaller ones hide each other's loads best (half as many waves as
-// items), but for the last axis, which runs two transforms on a tile. Measured
-// (us per iteration, waves): 2D 64x128^2 FP64 axis 1, 263 tiles of 32, 9 waves
-// 184.2, 8 waves 176.4 (nine fit a CU once, and seven tiles wait for a second
-// round); 48x150x131 FP64 axis 1, 405 tiles of 16, 10 waves 146.3, 8 waves
-// 140.7; 30x420x60 FP64 axis 1, 119 tiles, 5 waves 150.6, 16 waves 129.5; 3D
-// 32x64^3 FP64 time axis, 4292 tiles of 64, 4 waves 1825.0, 3 waves 1803.5;
-// 16x48x50x60 FP64 axis 1, 1653 tiles of 32, 4 waves 510.6, 2 waves 505.2.
+// and a few more for the loads, two take eight, up to four take four (three of
+// FP32 five, where that spares items a second round on a wave). With more,
+// smaller ones hide each other's loads best (half as many waves as items; five
+// FP32 workgroups can still have four each), but for the last axis, which runs
+// two transforms on a tile. Measured (us per iteration, waves): 2D 64x128^2 FP64
+// axis 1, 263 tiles of 32, 9 waves 184.2, 8 waves 176.4 (nine fit a CU once, and
+// seven tiles wait for a second round); 48x150x131 FP64 axis 1, 405 tiles of 16,
+// 10 waves 146.3, 8 waves 140.7; 30x420x60 FP64 axis 1, 119 tiles, 5 waves
+// 150.6, 16 waves 129.5; 3D 32x64^3 FP64 time axis, 4292 tiles of 64, 4 waves
+// 1825.0, 3 waves 1803.5; 16x48x50x60 FP64 axis 1, 1653 tiles of 32, 4 waves
+// 510.6, 2 waves 505.2. Mixed, three tiles to a CU, 4 / 5 waves: five items
+// 64x128^2 114.2 / 112.6, 80x64x250 121.0 / 119.5; six 75x126x143 128.8 / 127.6; eight
+// 139x102x123 170.1 / 170.9; four tiles and five items 64x30^3 267.4 / 269.4. Mixed, five tiles, 2 / 4
+// waves: four items 55x274x134 207.9 / 205.7 and 12 more axes, all faster with 4;
+// two items 16x251x142 87.4 / 87.2, 98x25x20x14 121.5 / 122.5.
 template <typename T>
 int pass_waves(int L, int64_t tiles, int cw, size_t smem, bool last) {
   const bool f32 = sizeof(T) == 4;
@@ -415,7 +421,7 @@ int pass_waves(int L, int64_t tiles, int cw, size_t smem, bool last) {
   else if (n == 2)
     w = items > 4 ? 8 : 4;
   else if (n <= 4)
-    w = f32 && items == 5 ? 5 : 4;
+    w = f32 && n == 3 && (items == 5 || items == 6) ? 5 : 4;
   else if (last || (f32 && n == 5))
     w = 4;
   else

@@ -1,6 +1,7 @@
-"""The rule for the tile widths of the transform passes, at both sides of its
-limits: a middle width below 256 tiles only beside a neighbour that has it.
-Widths change no bit."""
+"""The rule for the tile widths and waves of the transform passes, at both sides
+of its limits: a middle width below 256 tiles only beside a neighbour that has
+it, and five FP32 waves only where three workgroups share a CU. Widths and
+waves change no bit."""
 import numpy as np
 import pytest
 
@@ -16,6 +17,9 @@ WIDTHS = [((46, 24, 153), D64, {0: 16, 1: 16}), ((53, 49, 31, 1), MIX, {1: 16, 2
           ((30, 42, 22, 4), MIX, {0: 16, 1: 16, 2: 16}), ((28, 57, 18, 3), D64, {2: 16}),
           ((48, 150, 131), D64, {0: 32, 1: 32, 2: 32}), ((13, 41, 47, 11), MIX, {0: 32, 1: 32, 2: 32}),
           ((22, 26, 256), D64, {0: 32, 1: 32}), ((40, 120, 70), D64, {0: 32, 1: 16, 2: 32})]
+# grid, precision, axis, waves
+WAVES = [((64, 128, 128), MIX, 0, 5), ((75, 126, 143), MIX, 0, 5), ((64, 30, 30, 30), MIX, 0, 4),
+         ((139, 102, 123), MIX, 1, 4), ((64, 128, 128), D64, 0, 4)]
 
 
 def _plan(n, prec):
@@ -41,6 +45,13 @@ def test_widths(n, prec, widths):
     flip = [48 - cw[d] if d in widths else 0 for d in range(len(n))]  # 16 for 32 and 32 for 16
     B.dot_plan_set_schedule(plan, cw=flip)
     assert G.torch_mod().equal(a, _state(plan))
+    plan.close()
+
+
+@pytest.mark.parametrize("n,prec,a,waves", WAVES, ids=["x".join(map(str, c[0])) + "-" + "dm"[c[1]] for c in WAVES])
+def test_waves(n, prec, a, waves):
+    plan = _plan(n, prec)
+    assert B.dot_plan_get_schedule(plan)["waves"][a] == waves
     plan.close()
 
 
