@@ -17,11 +17,12 @@
 // alpha and beta alternate between two places like q does (iteration parity).
 //
 // Bound by memory: 2D moves 34 planes of 8 bytes per iteration (FP64) instead
-// of 58, and the sweep takes as long as one that only copies the same planes
-// (2D 64x256^2: 224 against 217-227 us mixed, 328 against 341-400 us FP64, 3.9
-// and 4.3 TB/s; the separate sweeps took 290 and 490 us). Nontemporal stores
-// made it slower (389 -> 425 us per iteration: the planes no longer wait in the
-// last-level cache), two slices of loads in flight changed nothing.
+// of 58. 2D 64x256^2: 278 us FP64 and 190 us mixed (the separate sweeps took 490
+// and 290), for 1154 and 696 MB if every element is moved once, 4.2 and 3.7 TB/s;
+// with the halo's reads the counters give 1.30 GB in FP64, 4.7 TB/s, where a 1 GiB
+// copy reaches 4.8. Nontemporal stores made it slower (389 -> 425 us per
+// iteration: the planes no longer wait in the last-level cache), two slices of
+// loads in flight changed nothing.
 #pragma once
 #include "geometry.hpp"
 #include "kernels_update.hpp"

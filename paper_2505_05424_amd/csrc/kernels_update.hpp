@@ -357,12 +357,6 @@ __device__ __forceinline__ void q_body(const Geo& g, const double* __restrict__ 
   }
 }
 
-// Right-hand side of the phi-step of Algorithm 2 per node, written to the
-// transform work plane: b = A^*(q - alpha/sigma) - c/sigma (zero extension
-// outside each staggered set) or, with DEFECT, the defect b - A^*A phi of the
-// FP64 phi (path-graph Laplacian / h_d^2 per axis, Neumann ends). The time
-// neighbours (q0 - alpha0/sigma at t-1, phi at t-1 and t) are carried, and
-// the loads of slice t+1 are issued before slice t is computed.
 // A^*A phi at node (t, x): the path-graph Laplacians / h_d^2 with Neumann ends.
 // phm, phn: phi at t - 1 and t + 1; phs[d]: phi at x - e_d and x + e_d.
 template <int D>
@@ -381,6 +375,12 @@ __device__ __forceinline__ double neg_laplacian(const Geo& g, int t, const int (
   return r;
 }
 
+// Right-hand side of the phi-step of Algorithm 2 per node, written to the
+// transform work plane: b = A^*(q - alpha/sigma) - c/sigma (zero extension
+// outside each staggered set) or, with DEFECT, the defect b - A^*A phi of the
+// FP64 phi (path-graph Laplacian / h_d^2 per axis, Neumann ends). The time
+// neighbours (q0 - alpha0/sigma at t-1, phi at t-1 and t) are carried, and
+// the loads of slice t+1 are issued before slice t is computed.
 template <typename T, int D>
 struct RhsSlice {
   T q0;                     // q0 at the cell t (t < n0)
