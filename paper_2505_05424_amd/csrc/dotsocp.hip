@@ -441,13 +441,17 @@ int pass_waves(int L, int64_t tiles, int cw, size_t smem, bool last) {
 // narrow one wins the more the fewer there are (19x180x128 FP64 axis 1, 81 tiles,
 // 82.1 / 86.5; 114x156x22 axis 0, 113, 76.0 / 78.8; but 120x38x111 axis 0, 137, 90.1 /
 // 87.6). Up to 256 tiles an axis other than the last takes the middle width only
-// with its neighbour (`paired`): passes of different widths one after the other
-// cost more than the coefficients save, or nothing is saved (16 on both against
-// 32 on the one: 46x24x153 FP64 axis 1 57.0 / 59.2, 44x28x123 52.6 / 54.4, 53x49x31x1 axis 2
-// 70.8 / 72.3 and mixed 62.0 / 64.6, 28x57x18x3 61.5 / 62.9 and 55.5 / 56.9; 32 on both: 13x41x47x11
-// FP64 95.4 / 92.2, mixed 80.5 / 76.2).
+// with its neighbour (`paired`) in 3D and, in FP64, up to kPairPoints points: there
+// passes of different widths one after the other cost more than the coefficients
+// save (16 on both against 32 on the one: 46x24x153 FP64 axis 1 57.0 / 59.2, 58x31x103
+// 53.7 / 55.4, 53x49x31x1 axis 2 70.8 / 72.3 and mixed 62.0 / 64.6, 31x47x25x4 73.8 / 76.5 and
+// 64.4 / 67.7; 32 on both: 13x41x47x11 FP64 95.4 / 92.2, mixed 80.5 / 76.2). In 2D longer
+// axes gain alone (FP64 152x74x39 axis 1 80.7 / 79.9; 26 from 35 to 64 points are between
+// 1.3% slower and 0.7% faster), and of 51 in mixed precision 48 (126x36x37 47.8 / 46.3, but
+// 89x29x87 52.4 / 52.7).
 constexpr int64_t kWideTiles = 4 * kPassCUs;
 constexpr int64_t kMidTiles = 150;
+constexpr int kPairPoints = 64;
 constexpr size_t kMidLds = 40 << 10;
 int choose_cw(int64_t lines, bool wide_ok, bool mid_ok, size_t mid_smem, bool paired) {
   if (wide_ok && (lines + kCW - 1) / kCW >= kWideTiles) return kCW;
@@ -494,6 +498,7 @@ struct AxisGeom {
 template <typename T>
 AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s, bool alone = false) {
   int64_t all_lines = 0;
+  int longest = 0;
   bool wide_ok = true, mid_ok = true, all_tri = true;
   const bool last = a == plans[0]->D;
   auto transformed = [&](const dot_plan* P) { return !(last && P->tri); };  // else eliminated
@@ -507,10 +512,13 @@ AxisGeom axis_geom(dot_plan* const* plans, int count, int a, const Sched& s, boo
     all_lines += plans[i]->lines[a];
     wide_ok = wide_ok && plans[i]->wide_ok[a];
     mid_ok = mid_ok && plans[i]->mid_ok[a];
+    longest = std::max(longest, plans[i]->g.N[a]);
     all_tri = all_tri && plans[i]->tri;
   }
   auto paired = [&]() {  // the neighbour by its own lines (`alone`)
-    return alone || last || plans[0]->D == 1 ||
+    const int D = plans[0]->D;
+    const bool needed = D == 3 || (D == 2 && sizeof(T) == 8 && longest <= kPairPoints);
+    return alone || last || !needed ||
            axis_geom<T>(plans, count, a == 0 ? 1 : a - 1, Sched(), true).cw > kCWNarrow;
   };
   AxisGeom ag;

@@ -1,7 +1,7 @@
 """The rule for the tile widths and waves of the transform passes, at both sides
-of its limits: a middle width below 256 tiles only beside a neighbour that has
-it, and five FP32 waves only where three workgroups share a CU. Widths and
-waves change no bit."""
+of its limits: short axes take a middle width below 256 tiles only beside a
+neighbour that has it, and five FP32 waves only where three workgroups share a
+CU. Widths and waves change no bit."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 D64, MIX = B.DOT_FP64, B.DOT_MIXED
 # grid, precision, axis -> tile width
-WIDTHS = [((46, 24, 153), D64, {0: 16, 1: 16}), ((53, 49, 31, 1), MIX, {1: 16, 2: 16}),
+WIDTHS = [((46, 24, 153), D64, {0: 16, 1: 16}), ((46, 24, 153), MIX, {0: 16, 1: 32}),
+          ((96, 63, 58), D64, {0: 16, 1: 16}), ((96, 64, 58), D64, {0: 16, 1: 32}), ((53, 49, 31, 1), MIX, {1: 16, 2: 16}),
           ((30, 42, 22, 4), MIX, {0: 16, 1: 16, 2: 16}), ((28, 57, 18, 3), D64, {2: 16}),
           ((48, 150, 131), D64, {0: 32, 1: 32, 2: 32}), ((13, 41, 47, 11), MIX, {0: 32, 1: 32, 2: 32}),
           ((22, 26, 256), D64, {0: 32, 1: 32}), ((40, 120, 70), D64, {0: 32, 1: 16, 2: 32})]
@@ -35,7 +36,7 @@ def _state(plan):
     return s.buf[:plan.info.off_w]
 
 
-@pytest.mark.parametrize("n,prec,widths", WIDTHS, ids=["x".join(map(str, c[0])) for c in WIDTHS])
+@pytest.mark.parametrize("n,prec,widths", WIDTHS, ids=["x".join(map(str, c[0])) + "-" + "dm"[c[1]] for c in WIDTHS])
 def test_widths(n, prec, widths):
     print(f"[case] widths {n} precision={prec}", flush=True)
     plan = _plan(n, prec)
